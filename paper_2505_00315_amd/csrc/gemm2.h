@@ -92,6 +92,13 @@ __device__ __forceinline__ u32x2 lds_read_tr16_at(const unsigned char* p) {
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(off), "i"(OFF) : "memory");
     return r;
 }
+// The same through the builtin: the compiler schedules it and waits for it like
+// any LDS read.  For tiles whose direct-to-LDS loads are issued by lds_load16
+// (invisible to the compiler), so that no wait on those is added.
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+__device__ __forceinline__ u32x2 lds_tr16(const unsigned char* p) {
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds_u8*)p));
+}
 // Wait for every outstanding LDS read of this wave.
 __device__ __forceinline__ void lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 // Wait until at most N LDS operations of this wave are outstanding (LDS
@@ -173,7 +180,7 @@ struct Gemm2Shape {
     static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
     static_assert(WM * WN == 4 && WTM % 16 == 0 && WTN % 16 == 0 && KC % 32 == 0, "tile shape");
     static_assert(A_UNITS % 256 == 0 && B_UNITS % 256 == 0, "whole instructions per wave");
-    static_assert((STAGES - 2) * (IA + IB) <= 63, "vmcnt range");
+    static_assert(STAGES >= 2 && (STAGES - 1) * (IA + IB) <= 63, "vmcnt range");
     static constexpr bool KG = G2Gather<P>::value, IL = G2Interleave<P>::value, ER = G2EpiRegs<P>::value;
     static constexpr bool CA = G2ChunkAdd<P>::value;
     static_assert(!KG || (!P::A_KCONTIG && !P::B_KCONTIG), "gathered k needs m-contiguous operands");
@@ -194,6 +201,18 @@ __device__ __forceinline__ void wait_vmcnt() {
     static_assert(N >= 0 && N <= 63, "vmcnt");
     // gfx9 s_waitcnt: vmcnt [3:0] and [15:14], expcnt [6:4] = 7, lgkmcnt [11:8] = 15
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
+}
+
+// Scheduling order of a step with NM MFMAs and NR LDS reads: the reads spread
+// evenly over the MFMAs.
+template <int NM, int NR, int I = 0>
+__device__ __forceinline__ void sched_mix() {
+    if constexpr (I < NM) {
+        constexpr int R = (NR * (I + 1)) / NM - (NR * I) / NM;
+        if constexpr (R > 0) __builtin_amdgcn_sched_group_barrier(0x100, R, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        sched_mix<NM, NR, I + 1>();
+    }
 }
 
 // One workgroup's tile of logical index `logical`.
@@ -328,124 +347,117 @@ __device__ __forceinline__ void gemm2_body(const typename P::Args& args, int log
         f.v = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(t + (row * LPR + (s ^ kswz(row, LPR))) * 16));
         return f;
     };
-    // m-contiguous fragment: two transposed reads, raw (see lds_read_tr16)
-    // (colstep 8 and odd: the interleaved pairs of A_INTERLEAVE)
+    // m-contiguous fragment: two transposed reads (colstep 8 and odd: the
+    // interleaved pairs of A_INTERLEAVE)
     auto frag_m = [&](const unsigned char* t, int mbase, int ks, auto u_tag, int colstep = 4, int odd = 0) {
         constexpr int U = decltype(u_tag)::value;
         const int mcol = mbase + colstep * (c16 & 3) + 4 * odd;
         const int u = mcol >> 3, half = (mcol >> 2) & 1;
         const int k0r = ks + 8 * g + (c16 >> 2);
-        const u32x2 lo = lds_read_tr16(t + (k0r * U + mswz<U>(k0r, u)) * 16 + 8 * half);
+        const u32x2 lo = lds_tr16(t + (k0r * U + mswz<U>(k0r, u)) * 16 + 8 * half);
         const int k1r = k0r + 4;
-        const u32x2 hi = lds_read_tr16(t + (k1r * U + mswz<U>(k1r, u)) * 16 + 8 * half);
-        return u32x4{lo.x, lo.y, hi.x, hi.y};
+        const u32x2 hi = lds_tr16(t + (k1r * U + mswz<U>(k1r, u)) * 16 + 8 * half);
+        Frag8<ST> f;
+        f.v = __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
+        return f;
     };
-    auto mfma_buf = [&](int bidx) {
+    // Operand fragments of one 32-k step.
+    struct Frags {
+        Frag8<ST> a[S::FM], b[S::FN];
+    };
+    auto load_frags = [&](Frags& f, int bidx, int ks) {
         const unsigned char* ta = smem + bidx * S::STAGE_BYTES;
         const unsigned char* tb = ta + S::A_BYTES;
 #pragma unroll
-        for (int ks = 0; ks < KC; ks += 32) {
-            Frag8<ST> fa[S::FM], fb[S::FN];
-            u32x4 ma[S::FM], mb[S::FN];  // raw m-contiguous fragments
-            if constexpr (!P::A_KCONTIG && !P::B_KCONTIG) {
+        for (int j = 0; j < S::FN; ++j) {
+            if constexpr (P::B_KCONTIG) f.b[j] = frag_k(tb, wn * S::WTN + j * 16 + c16, ks);
+            else f.b[j] = frag_m(tb, wn * S::WTN + j * 16, ks, std::integral_constant<int, NT / 8>{});
+        }
 #pragma unroll
-                for (int j = 0; j < S::FN; ++j)
-                    mb[j] = frag_m(tb, wn * S::WTN + j * 16, ks, std::integral_constant<int, NT / 8>{});
-            }
-#pragma unroll
-            for (int i = 0; i < S::FM; ++i) {
-                if constexpr (P::A_KCONTIG) fa[i] = frag_k(ta, wm * S::WTM + i * 16 + c16, ks);
-                else if constexpr (S::IL)
-                    ma[i] = frag_m(ta, wm * S::WTM + 32 * (i >> 1), ks, std::integral_constant<int, MT / 8>{}, 8, i & 1);
-                else ma[i] = frag_m(ta, wm * S::WTM + i * 16, ks, std::integral_constant<int, MT / 8>{});
-            }
-#pragma unroll
-            for (int j = 0; j < S::FN; ++j) {
-                if constexpr (P::B_KCONTIG) fb[j] = frag_k(tb, wn * S::WTN + j * 16 + c16, ks);
-                else if constexpr (P::A_KCONTIG)
-                    mb[j] = frag_m(tb, wn * S::WTN + j * 16, ks, std::integral_constant<int, NT / 8>{});
-            }
-            if constexpr (!P::A_KCONTIG && !P::B_KCONTIG) {
-                // Both operands by transposed reads: B's were issued first, so
-                // after the wait for A fragment i (2 reads each) the MFMAs of
-                // that row block can start while later reads are in flight.
-                static_assert(2 * (S::FM - 1) <= 15, "lgkmcnt range");
-#pragma unroll
-                for (int i = 0; i < S::FM; ++i) {
-                    lds_wait_le(2 * (S::FM - 1 - i));
-                    if (i == 0) {
-#pragma unroll
-                        for (int j = 0; j < S::FN; ++j) {
-                            lds_ready(mb[j]);
-                            fb[j].v = __builtin_bit_cast(bf16x8, mb[j]);
-                        }
-                    }
-                    lds_ready(ma[i]);
-                    fa[i].v = __builtin_bit_cast(bf16x8, ma[i]);
-#pragma unroll
-                    for (int j = 0; j < S::FN; ++j) mma8(acc[i][j], fa[i], fb[j]);
-                    __builtin_amdgcn_sched_barrier(0);  // keep these MFMAs before the next wait
-                }
-                continue;
-            }
-            if constexpr (!P::A_KCONTIG || !P::B_KCONTIG) {
-                lds_wait();
-#pragma unroll
-                for (int i = 0; i < S::FM; ++i)
-                    if constexpr (!P::A_KCONTIG) {
-                        lds_ready(ma[i]);
-                        fa[i].v = __builtin_bit_cast(bf16x8, ma[i]);
-                    }
-#pragma unroll
-                for (int j = 0; j < S::FN; ++j)
-                    if constexpr (!P::B_KCONTIG) {
-                        lds_ready(mb[j]);
-                        fb[j].v = __builtin_bit_cast(bf16x8, mb[j]);
-                    }
-            }
-#pragma unroll
-            for (int i = 0; i < S::FM; ++i)
-#pragma unroll
-                for (int j = 0; j < S::FN; ++j) {
-                    if constexpr (S::CA) {
-                        f32x4 part = zero4();
-                        mma8(part, fa[i], fb[j]);
-                        acc[i][j] += part;
-                    } else {
-                        mma8(acc[i][j], fa[i], fb[j]);
-                    }
-                }
+        for (int i = 0; i < S::FM; ++i) {
+            if constexpr (P::A_KCONTIG) f.a[i] = frag_k(ta, wm * S::WTM + i * 16 + c16, ks);
+            else if constexpr (S::IL)
+                f.a[i] = frag_m(ta, wm * S::WTM + 32 * (i >> 1), ks, std::integral_constant<int, MT / 8>{}, 8, i & 1);
+            else f.a[i] = frag_m(ta, wm * S::WTM + i * 16, ks, std::integral_constant<int, MT / 8>{});
         }
     };
+    auto mfma_step = [&](const Frags& f) {
+#pragma unroll
+        for (int i = 0; i < S::FM; ++i)
+#pragma unroll
+            for (int j = 0; j < S::FN; ++j) {
+                if constexpr (S::CA) {
+                    f32x4 part = zero4();
+                    mma8(part, f.a[i], f.b[j]);
+                    acc[i][j] += part;
+                } else {
+                    mma8(acc[i][j], f.a[i], f.b[j]);
+                }
+            }
+    };
 
-    // Pipeline: STAGES - 1 chunks in flight; per chunk one wait, one barrier,
-    // the loads of chunk c + STAGES - 1, then the MFMAs of chunk c.  Every
-    // wave issues exactly IA + IB loads per chunk, so the wait count is a
-    // constant.  An empty K range (no dense heads) issues nothing.
-    // The loop is unrolled by STAGES so that every stage buffer has a constant
-    // LDS offset: the compiler then sees that the loads in flight write other
-    // buffers than the one being read and does not wait for them.
-    // The only way out is after the MFMAs of the last chunk, through
-    // mfma_drain(): the compiler misses the MFMA result hazard on loop-exit
-    // edges, where it moves the accumulators to other registers.
+    // Pipeline.  STAGES - 1 chunks are in flight from global memory to LDS, and
+    // the fragments of the next 32-k step are read from LDS into a second
+    // register set while the MFMAs of the current step run, so that neither
+    // the LDS reads nor their latency add to the MFMA time (with one wave per
+    // SIMD nothing else would hide them).  Measured against reads and MFMAs in
+    // turn: the grouped backward of 128 heads, 256 rows each, d = 1024 85.4 ->
+    // 80.9 us, of 27 heads, 2048 rows each, d = 1280 148 -> 139 us.  At the last step of chunk c: wait
+    // for chunk c + 1, one barrier (every wave has then read all of chunk c),
+    // the loads of chunk c + STAGES into c's buffer, the reads of chunk c + 1's
+    // first step, the MFMAs.  Every wave issues exactly IA + IB loads per chunk,
+    // so the wait counts are constants; chunks past the end are not loaded, and
+    // the last STAGES - 2 waits are for everything.  An empty K range (no dense
+    // heads) issues nothing.
+    // The loop is unrolled so that every stage buffer has a constant LDS offset
+    // and every register set a constant name.  The last step reads the
+    // fragments of a chunk that does not exist (stale, never used), so that the
+    // only way out is after MFMAs that always run, through mfma_drain(): the
+    // compiler misses the MFMA result hazard on loop-exit edges, where it moves
+    // the accumulators to other registers.
+    constexpr int KS = KC / 32, L = S::IA + S::IB;
+    constexpr int UNROLL = STG * KS % 2 == 0 ? STG : 2 * STG;
     if (nchunks > 0) {
+        Frags fr[2];
 #pragma unroll
-        for (int s = 0; s < STG - 1; ++s) {
-            load_rows(s);
-            issue_buf(s, s);
+        for (int s = 0; s < STG; ++s) {
+            if (s < nchunks) {
+                load_rows(s);
+                issue_buf(s, s);
+            }
         }
-        load_rows(STG - 1);
-        for (int c0 = 0;; c0 += STG) {
+        load_rows(STG);
+        if (nchunks >= STG) wait_vmcnt<(STG - 1) * L>();
+        else wait_vmcnt<0>();
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        load_frags(fr[0], 0, 0);
+        for (int c0 = 0;; c0 += UNROLL) {
 #pragma unroll
-            for (int u = 0; u < STG; ++u) {
+            for (int u = 0; u < UNROLL; ++u) {
                 const int c = c0 + u;
-                wait_vmcnt<(STG - 2) * (S::IA + S::IB)>();
-                __syncthreads();  // chunk c is in LDS for every wave; chunk c-1's buffer is free
-                issue_buf(c + STG - 1, (u + STG - 1) % STG);
-                load_rows(c + STG);
-                __builtin_amdgcn_sched_barrier(0);
-                mfma_buf(u);
-                if constexpr (G2AHook<P>::value) P::a_tile_hook(args, m0, n0, smem + u * S::STAGE_BYTES, tid, hook_state);
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const int cur = (u * KS + ks) & 1;
+                    if (ks + 1 < KS) {
+                        load_frags(fr[cur ^ 1], u % STG, 32 * (ks + 1));
+                    } else {
+                        if constexpr (G2AHook<P>::value)
+                            P::a_tile_hook(args, m0, n0, smem + (u % STG) * S::STAGE_BYTES, tid, hook_state);
+                        if (c + STG <= nchunks) wait_vmcnt<(STG - 2) * L>();
+                        else wait_vmcnt<0>();
+                        __syncthreads();
+                        if (c + STG < nchunks) {
+                            issue_buf(c + STG, u % STG);
+                            load_rows(c + STG + 1);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        load_frags(fr[cur ^ 1], (u + 1) % STG, 0);
+                    }
+                    mfma_step(fr[cur]);
+                    sched_mix<S::FM * S::FN, (P::A_KCONTIG ? 1 : 2) * S::FM + (P::B_KCONTIG ? 1 : 2) * S::FN>();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 if (c + 1 == nchunks) {
                     mfma_drain();
                     goto pipeline_done;
