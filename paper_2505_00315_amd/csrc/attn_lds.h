@@ -23,16 +23,17 @@ __device__ __forceinline__ int vt_swz(int k) {  // V tile unit permutation (an i
     else return 2 * ((k >> 2) & 1);
 }
 
+// NMAX: an upper bound of n (a multiple of 32), which sizes the score registers.
 // Query block qb (local rows 16 qb ..) of a group of n rows whose keys are
 // LDS rows kbase .. kbase + n - 1 (kbase a multiple of 16); qf: the lane's query row (16 qb + lane % 16,
 // clamped) as B operand fragments; rw, A, lse: the group's r (or nullptr),
 // output rows and log-sum-exp.
-template <int DH>
+template <int DH, int NMAX = kAttnLdsMaxN>
 __device__ __forceinline__ void attn_lds_block(const unsigned char* Ks, const unsigned char* Vs, int kbase,
                                                const Frag8<uint16_t> (&qf)[DH / 32], int n, int causal, float scale,
                                                int qb, const float* rw, uint16_t* A, float* lse) {
     using ST = uint16_t;
-    constexpr int NMAX = kAttnLdsMaxN, U = DH / 8;
+    constexpr int U = DH / 8, SG = NMAX / 16 < 4 ? NMAX / 16 : 4;
     const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
     const int nqb = (n + 15) / 16, nkb = causal ? qb + 1 : nqb, q = 16 * qb + c16;
 
@@ -50,20 +51,37 @@ __device__ __forceinline__ void attn_lds_block(const unsigned char* Ks, const un
     }
     f32x4 s[NMAX / 16];
     float m = -__builtin_inff();
+    // SG key blocks at a time without a branch between them, so that their
+    // LDS reads and MFMAs overlap; blocks past the last one read rows that
+    // exist and are masked
 #pragma unroll
-    for (int sb = 0; sb < NMAX / 16; ++sb) {
-        s[sb] = f32x4{-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
-        if (sb < nkb) {
-            f32x4 acc = zero4();
+    for (int s0 = 0; s0 < NMAX / 16; s0 += SG) {
+        if (s0 < nkb) {
+            Frag8<ST> kf[SG][DH / 32];
 #pragma unroll
-            for (int st = 0; st < DH / 32; ++st) {
-                Frag8<ST> kf;
-                kf.v = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(kp[st] + sb * 16 * U * 16));
-                mma8(acc, kf, qf[st]);
+            for (int sb = 0; sb < SG; ++sb)
+#pragma unroll
+                for (int st = 0; st < DH / 32; ++st)
+                    kf[sb][st].v = __builtin_bit_cast(
+                        bf16x8, *reinterpret_cast<const uint4*>(kp[st] + (s0 + sb) * 16 * U * 16));
+            f32x4 acc[SG];
+#pragma unroll
+            for (int sb = 0; sb < SG; ++sb) acc[sb] = zero4();
+#pragma unroll
+            for (int st = 0; st < DH / 32; ++st)
+#pragma unroll
+                for (int sb = 0; sb < SG; ++sb) mma8(acc[sb], kf[sb][st], qf[st]);
+#pragma unroll
+            for (int sb = 0; sb < SG; ++sb) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    s[s0 + sb][i] = 16 * (s0 + sb) + 4 * g + i <= lim ? acc[sb][i] : -__builtin_inff();
+                m = fmaxf(m, fmaxf(fmaxf(s[s0 + sb][0], s[s0 + sb][1]), fmaxf(s[s0 + sb][2], s[s0 + sb][3])));
             }
+        } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s[sb][i] = 16 * sb + 4 * g + i <= lim ? acc[i] : -__builtin_inff();
-            m = fmaxf(m, fmaxf(fmaxf(s[sb][0], s[sb][1]), fmaxf(s[sb][2], s[sb][3])));
+            for (int sb = 0; sb < SG; ++sb)
+                s[s0 + sb] = f32x4{-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
         }
     }
     m = fmaxf(m, __shfl_xor(m, 16, 64));
@@ -103,21 +121,15 @@ __device__ __forceinline__ void attn_lds_block(const unsigned char* Ks, const un
             const float pv[8] = {s[2 * uu][0], s[2 * uu][1], s[2 * uu][2], s[2 * uu][3],
                                  s[2 * uu + 1][0], s[2 * uu + 1][1], s[2 * uu + 1][2], s[2 * uu + 1][3]};
             const Frag8<ST> pf = frag8_from<ST>(pv);
-            u32x4 vt[DH / 16];
+            Frag8<ST> vf[DH / 16];
 #pragma unroll
             for (int db = 0; db < DH / 16; ++db) {
-                const u32x2 lo = lds_read_tr16_at<32 * U * 16 * uu>(vp[db]);
-                const u32x2 hi = lds_read_tr16_at<32 * U * 16 * uu + 16 * U * 16>(vp[db]);
-                vt[db] = u32x4{lo.x, lo.y, hi.x, hi.y};
+                const u32x2 lo = lds_tr16(vp[db] + 32 * U * 16 * uu);
+                const u32x2 hi = lds_tr16(vp[db] + 32 * U * 16 * uu + 16 * U * 16);
+                vf[db].v = __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
             }
-            lds_wait();
 #pragma unroll
-            for (int db = 0; db < DH / 16; ++db) {
-                lds_ready(vt[db]);
-                Frag8<ST> vf;
-                vf.v = __builtin_bit_cast(bf16x8, vt[db]);
-                mma8(o[db], vf, pf);
-            }
+            for (int db = 0; db < DH / 16; ++db) mma8(o[db], vf[db], pf);
         }
     });
     mfma_drain();

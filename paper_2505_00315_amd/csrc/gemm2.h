@@ -47,7 +47,12 @@
 //   MIN_WAVES: waves per SIMD the register allocation must allow.
 //   CHUNK_ADD (k-contiguous A and B): each MFMA from zero, then one add.
 //   EPI_REGS (needs A_INTERLEAVE): no C tile; the engine calls
-//     store8(args, batch, m, n, x[8]) for M indices m .. m + 7 at column n.
+//     store8(args, batch, m, n, x[8]) for M indices m .. m + 7 at column n, or,
+//     where the policy has it, epi_acc<Gemm2Shape<P>>(args, batch, m0, n0, acc,
+//     wm, wn, tid, smem) with the wave's accumulators: acc[2 p][j][r] and
+//     acc[2 p + 1][j][r] are M indices wm WTM + 32 p + 8 g + r and + 4 + r at
+//     column wn WTN + 16 j + lane % 16 of the tile (g = lane / 16).  The
+//     stage buffers are free by then (EPI_LDS bytes from smem on).
 //   a_tile_hook(args, m0, n0, a_tile, tid, state) / a_hook_done(args, m0, n0,
 //     tid, state): called by every thread after the MFMAs of each k chunk with
 //     that chunk's A tile in LDS (k-contiguous layout above), and once after
@@ -154,6 +159,9 @@ template <class P> struct G2AHook<P, std::void_t<decltype(&P::a_tile_hook)>> : s
 template <class P, class = void> struct G2EpiRegs : std::false_type {};
 template <class P> struct G2EpiRegs<P, std::void_t<decltype(P::EPI_REGS)>> : std::bool_constant<P::EPI_REGS> {};
 
+template <class P, class = void> struct G2EpiAcc : std::false_type {};
+template <class P> struct G2EpiAcc<P, std::void_t<decltype(P::EPI_ACC)>> : std::bool_constant<P::EPI_ACC> {};
+
 // a_koff(args, batch, c) / b_koff(args, batch, c): element offset of k chunk c
 // from chunk 0 (k-contiguous operands whose k axis is made of segments, e.g.
 // heads, that are not adjacent in memory; the policy keeps KC within one
@@ -191,7 +199,7 @@ struct Gemm2Shape {
     // padded range) follows the stage buffers.
     static constexpr size_t lds_bytes(int ktab_rows = 0) {
         const size_t ops = (size_t)STAGES * STAGE_BYTES + (KG ? (size_t)ktab_rows * 8 : 0);
-        const size_t epi = ER ? 0 : ctile_bytes + P::EPI_LDS;
+        const size_t epi = ctile_bytes + P::EPI_LDS;
         return ops > epi ? ops : epi;
     }
 };
@@ -468,7 +476,11 @@ __device__ __forceinline__ void gemm2_body(const typename P::Args& args, int log
 pipeline_done:
     if constexpr (G2AHook<P>::value) P::a_hook_done(args, m0, n0, tid, hook_state);
     wait_vmcnt<0>();  // the trailing loads write into the buffers the C tile reuses
-    if constexpr (S::ER) {
+    if constexpr (G2EpiAcc<P>::value) {
+        static_assert(S::ER, "accumulator epilogue needs EPI_REGS");
+        __syncthreads();
+        P::template epi_acc<S>(args, batch, m0, n0, acc, wm, wn, tid, smem);
+    } else if constexpr (S::ER) {
         // lane: M indices 32 p + 8 g .. + 7 of the wave's rows, column c16 of block j
 #pragma unroll
         for (int p = 0; p < S::FM / 2; ++p)

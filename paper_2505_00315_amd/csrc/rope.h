@@ -10,13 +10,10 @@
 
 namespace mosa {
 
-// 8 consecutive columns c0 .. c0 + 7 (c0 % 8 == 0, c0 < DH/2) of a q or k
-// row at position pos: the 4 pairs they hold, rotated by +angle (sign 1) or
-// by -angle (sign -1, the transpose used by the backward pass).
-template <int DH>
-__device__ __forceinline__ void rope8(float (&x)[8], int c0, const float2* __restrict__ tab, int pos, float sign) {
-    const float2* t = tab + (size_t)pos * (DH / 4) + c0 / 2;
-    const float4 a = *reinterpret_cast<const float4*>(t), b = *reinterpret_cast<const float4*>(t + 2);
+// 8 consecutive columns of a q or k row, the 4 pairs they hold rotated by
+// their (cos, sin) in a, b by +angle (sign 1) or -angle (sign -1, the transpose
+// used by the backward pass).
+__device__ __forceinline__ void rope8_tab(float (&x)[8], const float4& a, const float4& b, float sign) {
     const float cs[4] = {a.x, a.z, b.x, b.z}, sn[4] = {a.y, a.w, b.y, b.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -24,6 +21,12 @@ __device__ __forceinline__ void rope8(float (&x)[8], int c0, const float2* __res
         x[2 * i] = u * cs[i] - v * s;
         x[2 * i + 1] = u * s + v * cs[i];
     }
+}
+// The same for columns c0 .. c0 + 7 (c0 % 8 == 0, c0 < DH/2) at position pos.
+template <int DH>
+__device__ __forceinline__ void rope8(float (&x)[8], int c0, const float2* __restrict__ tab, int pos, float sign) {
+    const float2* t = tab + (size_t)pos * (DH / 4) + c0 / 2;
+    rope8_tab(x, *reinterpret_cast<const float4*>(t), *reinterpret_cast<const float4*>(t + 2), sign);
 }
 
 // 4 consecutive columns d0 .. d0 + 3 (d0 % 4 == 0) of a dQ or dK row at
