@@ -371,30 +371,24 @@ __device__ __forceinline__ void attn_bwd_kv_tiled_body(unsigned char* smem, int 
             // from the row-major tiles: lane d columns 16 db + 4 (c16 % 4) ..
             // + 3 at query rows r0 and r0 + 16
             const int r0 = 32 * u + 4 * g + (c16 >> 2);
-            u32x4 at[DH / 16], qt[DH / 16];
+            Frag8<ST> at[DH / 16], qt[DH / 16];
 #pragma unroll
             for (int db = 0; db < DH / 16; ++db) {
                 const int mcol = 16 * db + 4 * (c16 & 3);
                 const int o0 = TL::off(r0, mcol), o1 = TL::off(r0 + 16, mcol);
-                const u32x2 alo = lds_read_tr16(reinterpret_cast<const unsigned char*>(dAs + o0));
-                const u32x2 ahi = lds_read_tr16(reinterpret_cast<const unsigned char*>(dAs + o1));
-                const u32x2 qlo = lds_read_tr16(reinterpret_cast<const unsigned char*>(Qs + o0));
-                const u32x2 qhi = lds_read_tr16(reinterpret_cast<const unsigned char*>(Qs + o1));
-                at[db] = u32x4{alo.x, alo.y, ahi.x, ahi.y};
-                qt[db] = u32x4{qlo.x, qlo.y, qhi.x, qhi.y};
+                const u32x2 alo = lds_tr16(reinterpret_cast<const unsigned char*>(dAs + o0));
+                const u32x2 ahi = lds_tr16(reinterpret_cast<const unsigned char*>(dAs + o1));
+                const u32x2 qlo = lds_tr16(reinterpret_cast<const unsigned char*>(Qs + o0));
+                const u32x2 qhi = lds_tr16(reinterpret_cast<const unsigned char*>(Qs + o1));
+                at[db].v = __builtin_bit_cast(bf16x8, u32x4{alo.x, alo.y, ahi.x, ahi.y});
+                qt[db].v = __builtin_bit_cast(bf16x8, u32x4{qlo.x, qlo.y, qhi.x, qhi.y});
             }
-            lds_wait();
 #pragma unroll
             for (int db = 0; db < DH / 16; ++db) {
-                lds_ready(at[db]);
-                lds_ready(qt[db]);
-                Frag8<ST> fa, fq;
-                fa.v = __builtin_bit_cast(bf16x8, at[db]);
-                fq.v = __builtin_bit_cast(bf16x8, qt[db]);
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb) {
-                    mma8(dVt[cb][db], fa, pf[cb]);
-                    mma8(dKt[cb][db], fq, dsf[cb]);
+                    mma8(dVt[cb][db], at[db], pf[cb]);
+                    mma8(dKt[cb][db], qt[db], dsf[cb]);
                 }
             }
         }
@@ -573,22 +567,18 @@ __device__ __forceinline__ void attn_bwd_q_tiled_body(unsigned char* smem, int b
             }
             // K^T over the keys of those slots, read transposed from the row-major tile
             const int r0 = 32 * u + 4 * g + (c16 >> 2);
-            u32x4 kt[DH / 16];
+            Frag8<ST> kt[DH / 16];
 #pragma unroll
             for (int db = 0; db < DH / 16; ++db) {
                 const int mcol = 16 * db + 4 * (c16 & 3);
-                const u32x2 lo = lds_read_tr16(reinterpret_cast<const unsigned char*>(Ks + TL::off(r0, mcol)));
-                const u32x2 hi = lds_read_tr16(reinterpret_cast<const unsigned char*>(Ks + TL::off(r0 + 16, mcol)));
-                kt[db] = u32x4{lo.x, lo.y, hi.x, hi.y};
+                const u32x2 lo = lds_tr16(reinterpret_cast<const unsigned char*>(Ks + TL::off(r0, mcol)));
+                const u32x2 hi = lds_tr16(reinterpret_cast<const unsigned char*>(Ks + TL::off(r0 + 16, mcol)));
+                kt[db].v = __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
             }
-            lds_wait();
 #pragma unroll
             for (int db = 0; db < DH / 16; ++db) {
-                lds_ready(kt[db]);
-                Frag8<ST> fk;
-                fk.v = __builtin_bit_cast(bf16x8, kt[db]);
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) mma8(dQt[cb][db], fk, dsf[cb]);
+                for (int cb = 0; cb < CB; ++cb) mma8(dQt[cb][db], kt[db], dsf[cb]);
             }
         }
         mfma_drain();  // the loop may exit right here
@@ -652,36 +642,55 @@ __global__ __launch_bounds__(64 * NWV, CB == 1 ? 3 : 2) void attn_bwd_tiled_both
 #undef MOSA_BWD_TILED_PARAMS
 #undef MOSA_BWD_TILED_ARGS
 
-// bf16, n <= 128: both passes in one workgroup of 8 waves per (b, h).  Q, K,
-// V and dA of all n rows go into LDS once (direct global->LDS loads, rows
-// with XOR-permuted 16-byte units), with lse and D.  Phase 1, wave w owns key
+// bf16, 16 < n <= 128: both passes in one workgroup of NMAX / 16 waves per
+// (b, h), NMAX = 32, 64 or 128 the smallest that holds n.  Q, K, V and dA of
+// all n rows go into LDS once (direct global->LDS loads, rows with
+// XOR-permuted 16-byte units), with lse and D.  Phase 1, wave w owns key
 // block w: S and dP with the key in the lane (B operands K and V from
 // registers), P and dS, dV^T += dA^T P and dK^T += Q^T dS 32 queries per MFMA
 // (dA^T and Q^T by transposed LDS reads in the query order of the P and dS
 // registers), and dS (bf16, the MFMA operand value) into an LDS tile
-// [query][key].  Phase 2, wave w owns query block w: dQ^T += K^T dS^T 32 keys
-// per MFMA from that tile.  No value is accumulated by more than one lane, so
-// the result is reproducible; the roundings are those of the two-pass kernels
-// (P and dS enter the MFMAs as bf16).
+// [key][query], the lane's 4 consecutive queries as one 8-byte write.  Phase
+// 2, wave w owns query block w: dQ^T += K^T dS^T 32 keys per MFMA, dS^T by
+// transposed reads of that tile.  No value is accumulated by more than one
+// lane, so the result is reproducible.  The work is short (two barriers, a few
+// MFMAs per wave), so what counts is how many workgroups share a CU: sized by
+// n, 64 rows take 41 KB of LDS and 4 waves where the 128-row form took 97 KB
+// and 8 waves, half of them idle (one workgroup per CU: BWD64_BEFORE), and
+// 32 rows 18 KB and 2 waves (before: two launches of one wave per 16 rows
+// from global memory, BWD32_BEFORE).
 constexpr int kAttnBwdLdsMaxN = 128;
 
-template <int DH>
+template <int DH, int NMAX_>
 struct AttnBwdLds {
-    static constexpr int NMAX = kAttnBwdLdsMaxN, LPR = DH / 8, NW = NMAX / 16;
+    static constexpr int NMAX = NMAX_, LPR = DH / 8, NW = NMAX / 16;
     static constexpr int TILE = NMAX * DH * 2;           // Q, K, V, dA tiles
-    static constexpr int DS_BYTES = NMAX * NMAX * 2;     // dS [query][key], 16 units per row
+    static constexpr int DS_U = NMAX / 8;                // 16-byte units per row of the dS tile
+    static constexpr int DS_BYTES = NMAX * NMAX * 2;     // dS [key][query]
     static constexpr size_t lds = 4 * (size_t)TILE + DS_BYTES + 2 * NMAX * 4;
+    // Unit permutation of dS row `key`: the 16 rows of an 8-byte write (two
+    // adjacent units) and the 8 rows of a transposed read spread over the
+    // pairs of units that share a bank position.
+    __device__ static int swz(int key) {
+        if constexpr (DS_U == 16) return 2 * (key & 7) + ((key >> 3) & 1);
+        else if constexpr (DS_U == 8) return (key & 7) ^ ((key >> 3) & 1);
+        else return 2 * ((key >> 2) & 1);
+    }
+    // byte offset of dS[key][q], q a multiple of 4
+    __device__ static int ds_off(int key, int q) {
+        return (key * DS_U + ((q >> 3) ^ swz(key))) * 16 + 2 * (q & 4);
+    }
 };
 
-template <int DH>
-__global__ __launch_bounds__(512) void attn_bwd_lds_kernel(const uint16_t* __restrict__ QKV,
+template <int DH, int NMAX_>
+__global__ __launch_bounds__(4 * NMAX_) void attn_bwd_lds_kernel(const uint16_t* __restrict__ QKV,
                                                            const uint16_t* __restrict__ dA,
                                                            const float* __restrict__ lse, const float* __restrict__ D,
                                                            int BH, int n, int causal, float scale,
                                                            uint16_t* __restrict__ dQKV, const int32_t* __restrict__ rI,
                                                            const float2* __restrict__ rtab) {
     using ST = uint16_t;
-    using L = AttnBwdLds<DH>;
+    using L = AttnBwdLds<DH, NMAX_>;
     constexpr int RS = 3 * DH, NMAX = L::NMAX, LPR = L::LPR, NW = L::NW, TILE = L::TILE;
     constexpr int PER = NMAX * LPR / (64 * NW);  // DMA instructions per wave per tile
     static_assert(PER >= 1 && NMAX * LPR % (64 * NW) == 0, "tile shape");
@@ -733,22 +742,24 @@ __global__ __launch_bounds__(512) void attn_bwd_lds_kernel(const uint16_t* __res
     // transposed read of 4 rows k .. k + 3 (k = kb0 + (c16 >> 2) per source lane) at columns mcol .. + 3
     auto tr4 = [&](const unsigned char* t, int k, int mcol) {
         const int un = mcol >> 3, half = (mcol >> 2) & 1;
-        return lds_read_tr16(t + (k * LPR + (un ^ kswz(k, LPR))) * 16 + 8 * half);
+        return lds_tr16(t + (k * LPR + (un ^ kswz(k, LPR))) * 16 + 8 * half);
+    };
+    auto frag = [](u32x2 lo, u32x2 hi) {
+        Frag8<ST> f;
+        f.v = __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
+        return f;
     };
     // A operand X^T (rows d = dbase + c16) over rows {kb + 4 g + i, kb + 16 + 4 g + i}
     // of a row-major tile: the order of two D-layout register blocks
     auto trA_pair = [&](const unsigned char* t, int dbase, int kb) {
         const int k0 = kb + 4 * g + (c16 >> 2), mcol = dbase + 4 * (c16 & 3);
-        const u32x2 lo = tr4(t, k0, mcol), hi = tr4(t, k0 + 16, mcol);
-        return u32x4{lo.x, lo.y, hi.x, hi.y};
+        return frag(tr4(t, k0, mcol), tr4(t, k0 + 16, mcol));
     };
     // A operand X^T over consecutive rows kb + 8 g .. + 7
     auto trA_run = [&](const unsigned char* t, int dbase, int kb) {
         const int k0 = kb + 8 * g + (c16 >> 2), mcol = dbase + 4 * (c16 & 3);
-        const u32x2 lo = tr4(t, k0, mcol), hi = tr4(t, k0 + 4, mcol);
-        return u32x4{lo.x, lo.y, hi.x, hi.y};
+        return frag(tr4(t, k0, mcol), tr4(t, k0 + 4, mcol));
     };
-    auto ds_unit = [](int q, int key8) { return q * 16 + ((key8 >> 3) ^ (q & 15)); };  // dS tile, 16-byte unit
 
     const int nb = (n + 15) / 16;
     // With 8 blocks the causal work of block b is 8 - b (phase 1) or b + 1
@@ -770,56 +781,51 @@ __global__ __launch_bounds__(512) void attn_bwd_lds_kernel(const uint16_t* __res
 #pragma unroll
         for (int db = 0; db < DH / 16; ++db) dKt[db] = dVt[db] = zero4();
         for (int u = causal ? kb / 2 : 0; 2 * u < nb; ++u) {
-            float p[2][4], ds[2][4];
+            // S and dP of both query blocks of the pair (rows past n hold row
+            // n - 1 again: finite, masked below)
+            f32x4 s[2], dp[2];
+#pragma unroll
+            for (int hq = 0; hq < 2; ++hq) s[hq] = dp[hq] = zero4();
+#pragma unroll
+            for (int st = 0; st < DH / 32; ++st)
+#pragma unroll
+                for (int hq = 0; hq < 2; ++hq) {
+                    const int row = 32 * u + 16 * hq + c16;
+                    mma8(s[hq], frag_k(Qs, row, st), kf[st]);
+                    mma8(dp[hq], frag_k(dAs, row, st), vf[st]);
+                }
+            float pv8[8], ds8[8];
 #pragma unroll
             for (int hq = 0; hq < 2; ++hq) {
-                const int qb = 2 * u + hq;
-                f32x4 s = zero4(), dp = zero4();
-                if (qb < nb) {
-#pragma unroll
-                    for (int st = 0; st < DH / 32; ++st) {
-                        mma8(s, frag_k(Qs, 16 * qb + c16, st), kf[st]);
-                        mma8(dp, frag_k(dAs, 16 * qb + c16, st), vf[st]);
-                    }
-                }
-                mfma_drain();
+                const int q0 = 32 * u + 16 * hq + 4 * g;
+                const float4 lq = *reinterpret_cast<const float4*>(lse_s + q0), dq = *reinterpret_cast<const float4*>(D_s + q0);
+                const float l4[4] = {lq.x, lq.y, lq.z, lq.w}, d4[4] = {dq.x, dq.y, dq.z, dq.w};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int q = 16 * qb + 4 * g + i;
-                    const bool ok = qb < nb && q >= qmin && q < n;
-                    const float pv = ok ? __builtin_amdgcn_exp2f(fmaf(s[i], c2, -lse_s[q & (NMAX - 1)])) : 0.f;
-                    const float dsv = pv * (dp[i] - D_s[q & (NMAX - 1)]);
-                    p[hq][i] = pv;
-                    ds[hq][i] = dsv;
-                    if (qb < nb) {
-                        ST* dst = reinterpret_cast<ST*>(dSs + ds_unit(q, key) * 16) + (key & 7);
-                        *dst = f32_to_bf16(dsv);
-                    }
+                    const bool ok = q0 + i >= qmin && q0 + i < n;
+                    const float pv = ok ? __builtin_amdgcn_exp2f(fmaf(s[hq][i], c2, -l4[i])) : 0.f;
+                    pv8[4 * hq + i] = pv;
+                    ds8[4 * hq + i] = pv * (dp[hq][i] - d4[i]);
                 }
             }
-            // dV^T += dA^T P, dK^T += Q^T dS over the 32 queries 32 u + {4 g + i, 16 + 4 g + i}
-            const float pv8[8] = {p[0][0], p[0][1], p[0][2], p[0][3], p[1][0], p[1][1], p[1][2], p[1][3]};
-            const float ds8[8] = {ds[0][0], ds[0][1], ds[0][2], ds[0][3], ds[1][0], ds[1][1], ds[1][2], ds[1][3]};
             const Frag8<ST> pf = frag8_from<ST>(pv8), dsf = frag8_from<ST>(ds8);
-            u32x4 at[DH / 16], qt[DH / 16];
+            const uint4 dsu = __builtin_bit_cast(uint4, dsf.v);
+            *reinterpret_cast<uint2*>(dSs + L::ds_off(key, 32 * u + 4 * g)) = make_uint2(dsu.x, dsu.y);
+            *reinterpret_cast<uint2*>(dSs + L::ds_off(key, 32 * u + 16 + 4 * g)) = make_uint2(dsu.z, dsu.w);
+            // dV^T += dA^T P, dK^T += Q^T dS over the 32 queries 32 u + {4 g + i, 16 + 4 g + i}
+            Frag8<ST> at[DH / 16], qt[DH / 16];
 #pragma unroll
             for (int db = 0; db < DH / 16; ++db) {
                 at[db] = trA_pair(dAs, 16 * db, 32 * u);
                 qt[db] = trA_pair(Qs, 16 * db, 32 * u);
             }
-            lds_wait();
 #pragma unroll
             for (int db = 0; db < DH / 16; ++db) {
-                lds_ready(at[db]);
-                lds_ready(qt[db]);
-                Frag8<ST> fa, fq;
-                fa.v = __builtin_bit_cast(bf16x8, at[db]);
-                fq.v = __builtin_bit_cast(bf16x8, qt[db]);
-                mma8(dVt[db], fa, pf);
-                mma8(dKt[db], fq, dsf);
+                mma8(dVt[db], at[db], pf);
+                mma8(dKt[db], qt[db], dsf);
             }
+            mfma_drain();  // the loop may exit right here
         }
-        mfma_drain();
         if (key < n) {
             ST* out = dQKV + (base + key) * RS;
             const int pos = rtab ? (rI ? rI[base + key] : key) : 0;
@@ -844,25 +850,19 @@ __global__ __launch_bounds__(512) void attn_bwd_lds_kernel(const uint16_t* __res
         for (int db = 0; db < DH / 16; ++db) dQt[db] = zero4();
         const int nk = causal ? 16 * (qb + 1) : 16 * nb;
         for (int u = 0; 32 * u < nk; ++u) {
-            // dS^T[keys 32 u + 8 g .. + 7][q] = dS[q][...]; key blocks past the
-            // last one were never written and count as zero
-            const int k8 = 32 * u + 8 * g;
-            Frag8<ST> sf;
-            sf.v = __builtin_bit_cast(bf16x8, k8 < 16 * nb ? *reinterpret_cast<const uint4*>(dSs + ds_unit(q, k8) * 16)
-                                                           : make_uint4(0u, 0u, 0u, 0u));
-            u32x4 kt[DH / 16];
+            // dS^T[keys 32 u + 8 g .. + 7][q]: transposed reads of 4 + 4 key
+            // rows (D columns q = c16).  Key blocks past the last one were
+            // never written and count as zero.
+            const int k0 = 32 * u + 8 * g + (c16 >> 2), q0 = 16 * qb + 4 * (c16 & 3);
+            Frag8<ST> sf = frag(lds_tr16(dSs + L::ds_off(k0, q0)), lds_tr16(dSs + L::ds_off(k0 + 4, q0)));
+            if (32 * u + 8 * g >= 16 * nb) sf = frag8_zero<ST>();
+            Frag8<ST> kt[DH / 16];
 #pragma unroll
             for (int db = 0; db < DH / 16; ++db) kt[db] = trA_run(Ks, 16 * db, 32 * u);
-            lds_wait();
 #pragma unroll
-            for (int db = 0; db < DH / 16; ++db) {
-                lds_ready(kt[db]);
-                Frag8<ST> fk;
-                fk.v = __builtin_bit_cast(bf16x8, kt[db]);
-                mma8(dQt[db], fk, sf);
-            }
+            for (int db = 0; db < DH / 16; ++db) mma8(dQt[db], kt[db], sf);
+            mfma_drain();  // the loop may exit right here
         }
-        mfma_drain();
         if (q < n) {
             ST* out = dQKV + (base + q) * RS;
             const int pos = rtab ? (rI ? rI[base + q] : q) : 0;
@@ -1025,17 +1025,26 @@ int launch_t(const ST* QKV, const ST* dA, const float* lse, const float* D, int 
                            dQKV, rI, rtab);
         return hipGetLastError() == hipSuccess ? 0 : -1;
       }
-      if (n > 32 && n <= kAttnBwdLdsMaxN && window == 0) {
+      if (n <= kAttnBwdLdsMaxN && window == 0) {
         // both passes in one launch: the call for the dQ pass has nothing left to do
         if (pass == 1) return 0;
-        auto kern = dh == 64 ? attn_bwd_lds_kernel<64> : attn_bwd_lds_kernel<32>;
-        const size_t lds = dh == 64 ? AttnBwdLds<64>::lds : AttnBwdLds<32>::lds;
-        if (allow_lds((const void*)kern, lds)) return -1;
-        hipLaunchKernelGGL(kern, dim3(BH), dim3(512), lds, stream, QKV, dA, lse, D, BH, n, causal, scale, dQKV, rI,
-                           rtab);
-        return hipGetLastError() == hipSuccess ? 0 : -1;
+        auto go = [&](auto dht, auto nmt) {
+            constexpr int DH = decltype(dht)::value, NM = decltype(nmt)::value;
+            auto kern = attn_bwd_lds_kernel<DH, NM>;
+            constexpr size_t lds = AttnBwdLds<DH, NM>::lds;
+            if (allow_lds((const void*)kern, lds)) return -1;
+            hipLaunchKernelGGL(kern, dim3(BH), dim3(4 * NM), lds, stream, QKV, dA, lse, D, BH, n, causal, scale, dQKV,
+                               rI, rtab);
+            return hipGetLastError() == hipSuccess ? 0 : -1;
+        };
+        auto size = [&](auto dht) {
+            if (n <= 32) return go(dht, std::integral_constant<int, 32>{});
+            if (n <= 64) return go(dht, std::integral_constant<int, 64>{});
+            return go(dht, std::integral_constant<int, 128>{});
+        };
+        return dh == 64 ? size(std::integral_constant<int, 64>{}) : size(std::integral_constant<int, 32>{});
       }
-      if (n > 32 || window > 0) {
+      {
         // 4 waves per workgroup, 16 CB owned rows per wave.  Two column
         // blocks (half the LDS reads per MFMA, 2 waves per SIMD) where the
         // rows are long (n >= 1024, no window) and the blocks still give
@@ -1063,39 +1072,34 @@ int launch_t(const ST* QKV, const ST* dA, const float* lse, const float* D, int 
 #undef MOSA_ATTN_BWD_T
         return hipGetLastError() == hipSuccess ? 0 : -1;
       }
-    }
-    if (pass == 2)
-        return launch_t<ST>(QKV, dA, lse, D, BH, n, dh, causal, window, dQKV, rI, rtab, 0, stream) |
-               launch_t<ST>(QKV, dA, lse, D, BH, n, dh, causal, window, dQKV, rI, rtab, 1, stream);
-    const int tasks = BH * ((n + 15) / 16);
-    dim3 grid((tasks + 3) / 4), block(256);
-#define MOSA_ATTN_BWD(KERN, DHV)                                                                     \
-    do {                                                                                              \
-        auto kern = window > 0 ? KERN<ST, DHV, true> : KERN<ST, DHV, false>;                          \
-        hipLaunchKernelGGL(kern, grid, block, 0, stream, QKV, dA, lse, D, BH, n, causal, lb, scale, dQKV, rI, rtab); \
-    } while (0)
-    if (pass == 0) {
-        if (dh == 64) MOSA_ATTN_BWD(attn_bwd_kv_kernel, 64);
-        else MOSA_ATTN_BWD(attn_bwd_kv_kernel, 32);
     } else {
-        if (dh == 64) MOSA_ATTN_BWD(attn_bwd_q_kernel, 64);
-        else MOSA_ATTN_BWD(attn_bwd_q_kernel, 32);
-    }
+      if (pass == 2)
+          return launch_t<ST>(QKV, dA, lse, D, BH, n, dh, causal, window, dQKV, rI, rtab, 0, stream) |
+                 launch_t<ST>(QKV, dA, lse, D, BH, n, dh, causal, window, dQKV, rI, rtab, 1, stream);
+      const int tasks = BH * ((n + 15) / 16);
+      dim3 grid((tasks + 3) / 4), block(256);
+#define MOSA_ATTN_BWD(KERN, DHV)                                                                     \
+      do {                                                                                              \
+          auto kern = window > 0 ? KERN<ST, DHV, true> : KERN<ST, DHV, false>;                          \
+          hipLaunchKernelGGL(kern, grid, block, 0, stream, QKV, dA, lse, D, BH, n, causal, lb, scale, dQKV, rI, rtab); \
+      } while (0)
+      if (pass == 0) {
+          if (dh == 64) MOSA_ATTN_BWD(attn_bwd_kv_kernel, 64);
+          else MOSA_ATTN_BWD(attn_bwd_kv_kernel, 32);
+      } else {
+          if (dh == 64) MOSA_ATTN_BWD(attn_bwd_q_kernel, 64);
+          else MOSA_ATTN_BWD(attn_bwd_q_kernel, 32);
+      }
 #undef MOSA_ATTN_BWD
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+      return hipGetLastError() == hipSuccess ? 0 : -1;
+    }
 }
 
 }  // namespace
 
 // One launch for both passes where a kernel does both (bf16: the one-wave
-// kernel for n <= 16, the LDS kernel for 32 < n <= its limit, the tiled
-// kernels otherwise), else the two passes.
-template <typename ST>
-bool both_in_one(int n, int window) {
-    if constexpr (sizeof(ST) == 2) return n > 32 || window > 0 || n <= 16;
-    return false;
-}
-
+// kernel for n <= 16, the LDS kernels up to their limit, the tiled kernels
+// beyond and with a window), else the two passes (fp32).
 int launch_attn_bwd(int dtype, const void* QKV, const void* dA, const float* lse, const float* D, int BH, int n,
                     int dh, int causal, int window, void* dQKV, const int32_t* rope_I, const float2* rope,
                     int dense, const Marker& mk, hipStream_t stream) {
@@ -1106,7 +1110,7 @@ int launch_attn_bwd(int dtype, const void* QKV, const void* dA, const float* lse
     };
     auto go = [&](auto tag) {
         using ST = decltype(tag);
-        if (both_in_one<ST>(n, window)) {
+        if constexpr (sizeof(ST) == 2) {
             const int e = run(tag, 2);
             return e | mk(dense ? "attn_bwd_dense" : "attn_bwd");
         }
