@@ -656,9 +656,10 @@ __global__ __launch_bounds__(64 * NWV, CB == 1 ? 3 : 2) void attn_bwd_tiled_both
 // lane, so the result is reproducible.  The work is short (two barriers, a few
 // MFMAs per wave), so what counts is how many workgroups share a CU: sized by
 // n, 64 rows take 41 KB of LDS and 4 waves where the 128-row form took 97 KB
-// and 8 waves, half of them idle (one workgroup per CU: BWD64_BEFORE), and
-// 32 rows 18 KB and 2 waves (before: two launches of one wave per 16 rows
-// from global memory, BWD32_BEFORE).
+// and 8 waves, half of them idle (512 groups of 64 rows: 15.0 -> 10.1 us;
+// 1744 beside the dense heads' kernels 121 -> 52 us), and 32 rows take 18 KB
+// and 2 waves (96 groups: 6.8 us, against 27 + 7 us for two launches of one
+// wave per 16 rows from global memory).
 constexpr int kAttnBwdLdsMaxN = 128;
 
 template <int DH, int NMAX_>
