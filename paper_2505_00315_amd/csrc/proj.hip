@@ -267,6 +267,13 @@ struct QkvAttnPolicy : QkvPolicy2<DH, RT> {
     }
 };
 
+// Rows per tile of the gathered heads: 64 where 128-row tiles would be half
+// empty or too few to give every CU one (24 tiles of 12 heads, 256 rows each:
+// 28.2 us with 128 rows, 21.3 with 64; 17 half-empty ones 10.1 and 7.3), else
+// 128, which reads the weights half as often (256 tiles: 30.5 us with 128
+// rows, 33.9 with 64; 872: 105 and 110).
+inline bool narrow_rows(int M, int H) { return M <= 64 || (long long)H * ((M + 127) / 128) < 256; }
+
 template <typename ST, int DH>
 int run(const ST* X, const int32_t* I, const ST* Wq, const ST* Wk, const ST* Wv, int B, int T, int d, int H, int n,
         ST* out, const float2* rope, int narrow, hipStream_t stream) {
@@ -276,7 +283,7 @@ int run(const ST* X, const int32_t* I, const ST* Wq, const ST* Wk, const ST* Wv,
             const typename P::Args a{X, I, Wq, Wk, Wv, out, T, d, H, n, B * n, rope, make_fastdiv(n)};
             return launch_gemm2<P>(a, P::row_tiles(B * n) * H, stream);
         };
-        return narrow ? go(std::integral_constant<int, 64>{}) : go(std::integral_constant<int, 128>{});
+        return narrow || (I && narrow_rows(B * n, H)) ? go(std::integral_constant<int, 64>{}) : go(std::integral_constant<int, 128>{});
     } else {
         using P = QkvPolicy<ST, DH>;
         typename P::Args a{X, I, Wq, Wk, Wv, out, T, d, H, n, B * n, (B * n + P::MT - 1) / P::MT, rope};
@@ -305,9 +312,8 @@ int launch_qkv_attn(int dtype, const void* X, const int32_t* I, const void* Wq, 
         a.scale = scale;
         return launch_gemm2<P>(a, P::row_tiles(B * n) * H, stream);
     };
-    // at most 64 rows per head (B n <= 64): 64-row tiles instead of half-empty
-    // 128-row ones (measured equal or slower for more rows)
-    if ((long long)B * n <= 64)
+    // 64-row tiles where the 128-row ones would be half empty or leave CUs idle
+    if (n < 128 && narrow_rows(B * n, H))
         return dh == 64 ? go(std::integral_constant<int, 64>{}, std::integral_constant<int, 64>{})
                         : go(std::integral_constant<int, 32>{}, std::integral_constant<int, 64>{});
     return dh == 64 ? go(std::integral_constant<int, 64>{}, std::integral_constant<int, 128>{})
