@@ -21,7 +21,6 @@
 #include "attn_lds.h"
 #include "gemm2.h"
 #include "kernels.h"
-#include "tiles.h"
 
 namespace mosa {
 
@@ -111,12 +110,131 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(const ST* __restrict__ QK
     }
 }
 
-// Tiled variant for n > 32 (and every local-window head): a workgroup owns
-// 16 NWV query rows of one (b,h), 16 per wave (128 rows for bf16 with
-// 64-wide heads, else 64), and walks the keys in tiles of 64 staged in LDS
-// once for all its waves: K row-major (A operand of S^T = K Q^T) and V
-// (A operand of O^T += V^T P^T, K = 32 keys per MFMA, P^T straight from the
-// S^T registers; bf16 keeps V row-major and reads it transposed).  Online
+// fp32 storage: one workgroup of NW waves per block of 16 queries of one (b, h).
+// The waves take the allowed key blocks in turn (wave w the blocks w, w + NW,
+// ...) from global memory, each with its own online softmax (log2 units), and
+// the partial (max, sum, O) are combined in wave order through LDS
+// (reproducible).  As in the backward, few short heads make the latency of the
+// block loop and the share of the chip in use the bound: a workgroup per 64
+// queries walking the keys in LDS tiles took 38 us on 4 heads of 512 rows (32
+// workgroups), this form 16 us.
+constexpr int kAttnF32MaxWaves = 8;
+
+template <int DH>
+struct AttnF32 {
+    static constexpr int NDB = DH / 16;
+    static constexpr size_t lds(int nw) { return (size_t)nw * (NDB * 64 * sizeof(float4) + 2 * 16 * sizeof(float)); }
+};
+
+template <int DH, bool WIN>
+__global__ __launch_bounds__(64 * kAttnF32MaxWaves) void attn_fwd_f32_kernel(const float* __restrict__ QKV, int BH,
+                                                                             int n, int causal, int lb, float scale,
+                                                                             const float* __restrict__ rw,
+                                                                             float* __restrict__ A,
+                                                                             float* __restrict__ lse) {
+    using ST = float;
+    constexpr int RS = 3 * DH, NDB = DH / 16;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int g = lane >> 4, c16 = lane & 15;
+    float4* po = reinterpret_cast<float4*>(smem);                      // [nw][NDB][64]
+    float* pm = reinterpret_cast<float*>(po + (size_t)nw * NDB * 64);  // [nw][16] running max
+    float* pl = pm + 16 * nw;                                          // [nw][16] sum
+    const int nqb = (n + 15) / 16;
+    // the blocks with the most keys first
+    const int bh = blockIdx.x % BH, qb = causal ? nqb - 1 - blockIdx.x / BH : blockIdx.x / BH, q0 = 16 * qb;
+    const ST* Qp = QKV + (size_t)bh * n * RS;
+    const ST* Kp = Qp + DH;
+    const ST* Vp = Qp + 2 * DH;
+
+    const int q = q0 + c16;  // this lane's query
+    Frag8<ST> qf[DH / 32];
+#pragma unroll
+    for (int s = 0; s < DH / 32; ++s)
+        qf[s] = q < n ? frag8_load<ST>(Qp + (size_t)q * RS + s * 32 + 8 * g) : frag8_zero<ST>();
+
+    const float c2 = scale * 1.44269504088896341f;
+    float m_run = -__builtin_inff(), l_run = 0.f;
+    f32x4 o[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) o[db] = zero4();
+
+    const int kv_end = causal ? min(n, q0 + 16) : n;
+    for (int j0 = (WIN && causal ? max(0, q0 - lb) / 16 * 16 : 0) + 16 * wave; j0 < kv_end; j0 += 16 * nw) {
+        f32x4 s = zero4();
+        const int kr = j0 + c16;
+#pragma unroll
+        for (int st = 0; st < DH / 32; ++st) {
+            const Frag8<ST> kf = kr < n ? frag8_load<ST>(Kp + (size_t)kr * RS + st * 32 + 8 * g) : frag8_zero<ST>();
+            mma8(s, kf, qf[st]);
+        }
+        float sc[4], mloc = -__builtin_inff();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = j0 + 4 * g + i;
+            const bool ok = j < n && (!causal || (j <= q && (!WIN || q - j <= lb)));
+            sc[i] = ok ? s[i] * c2 : -__builtin_inff();
+            mloc = fmaxf(mloc, sc[i]);
+        }
+        mloc = rows4_max(mloc);
+        // a query may have no allowed key in this wave's blocks so far (max
+        // -inf): it then adds nothing
+        const float m_new = fmaxf(m_run, mloc), m_use = m_new == -__builtin_inff() ? 0.f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
+        float p[4], lsum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = __builtin_amdgcn_exp2f(sc[i] - m_use);
+            lsum += p[i];
+        }
+        l_run = l_run * alpha + rows4_sum(lsum);
+        m_run = m_new;
+        const Frag4<ST> pf = frag4_from<ST>(p);
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) {
+            o[db] *= alpha;
+            float vv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = j0 + 4 * g + i;
+                vv[i] = j < n ? Vp[(size_t)j * RS + db * 16 + c16] : 0.f;
+            }
+            mma4(o[db], frag4_from<ST>(vv), pf);
+        }
+        mfma_drain();  // the loop may exit right here
+    }
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+        po[(wave * NDB + db) * 64 + lane] = make_float4(o[db][0], o[db][1], o[db][2], o[db][3]);
+    if (g == 0) {
+        pm[16 * wave + c16] = m_run;
+        pl[16 * wave + c16] = l_run;
+    }
+    __syncthreads();
+    if (q >= n) return;
+    // every query has an allowed key, so the maximum over the waves is finite
+    float M = -__builtin_inff(), L = 0.f;
+    for (int w = 0; w < nw; ++w) M = fmaxf(M, pm[16 * w + c16]);
+    for (int w = 0; w < nw; ++w) L += pl[16 * w + c16] * __builtin_amdgcn_exp2f(pm[16 * w + c16] - M);
+    const float inv = (rw ? rw[(size_t)bh * n + q] : 1.f) / L;
+    for (int db = wave; db < NDB; db += nw) {
+        float x[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < nw; ++w) {
+            const float f = __builtin_amdgcn_exp2f(pm[16 * w + c16] - M);
+            const float4 v = po[(w * NDB + db) * 64 + lane];
+            x[0] += v.x * f; x[1] += v.y * f; x[2] += v.z * f; x[3] += v.w * f;
+        }
+        *reinterpret_cast<float4*>(A + ((size_t)bh * n + q) * DH + db * 16 + 4 * g) =
+            make_float4(x[0] * inv, x[1] * inv, x[2] * inv, x[3] * inv);
+    }
+    if (wave == 0 && g == 0) lse[(size_t)bh * n + q] = M * 0.69314718055994531f + logf(L);  // ln 2
+}
+
+// Tiled variant for bf16 32-wide heads with n > 128 or a local window: a
+// workgroup owns 16 NWV query rows of one (b,h), 16 per wave, and walks the
+// keys in tiles of 64 staged in LDS once for all its waves: K row-major (A
+// operand of S^T = K Q^T) and V (A operand of O^T += V^T P^T, K = 32 keys per
+// MFMA, P^T straight from the S^T registers, V read transposed).  Online
 // softmax in log2 units.  The next tile's global loads are in flight while
 // the current one is processed.  Causal blocks are launched heaviest first.
 template <typename ST, int DH, bool WIN, int NWV>
@@ -126,12 +244,11 @@ __global__ __launch_bounds__(64 * NWV) void attn_fwd_tiled_kernel(const ST* __re
     constexpr int NT = 64 * NWV, QB = 16 * NWV, KB = 64, RS = 3 * DH;
     constexpr int PAD = 16 / (int)sizeof(ST);
     constexpr int LDR = DH + PAD;   // row-major K rows (and the output staging)
-    constexpr int LDT = KB + 4;     // transposed V rows (keys), quad reads stay aligned
     constexpr int VPR = DH / 8;     // Vec8 per row
     constexpr int PER = KB * VPR / NT;
     static_assert(PER >= 1 && KB * VPR % NT == 0, "tile shape");
     __shared__ __attribute__((aligned(16))) ST Ks[(KB > QB ? KB : QB) * LDR];  // K tile, then the output rows
-    __shared__ __attribute__((aligned(16))) ST Vt[DH * LDT];
+    __shared__ __attribute__((aligned(16))) unsigned char Vs[KB * DH * 2];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, c16 = lane & 15;
@@ -169,21 +286,14 @@ __global__ __launch_bounds__(64 * NWV) void attn_fwd_tiled_kernel(const ST* __re
             vreg[p] = vec8_load<ST>(Vp + row * RS + dc);
         }
     };
-    // bf16: V rows stay row-major (16-byte units permuted per key row by
-    // vt_swz) and are read transposed (ds_read_b64_tr_b16), as in attn_lds.h
-    unsigned char* const Vs = reinterpret_cast<unsigned char*>(Vt);
-    static_assert(sizeof(ST) != 2 || DH * LDT * 2 >= KB * DH * 2, "V tile fits");
+    // V rows stay row-major (16-byte units permuted per key row by vt_swz)
+    // and are read transposed (ds_read_b64_tr_b16), as in attn_lds.h
     auto store_tile = [&]() {
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
             const int v = tid + NT * p, key = v / VPR, dc = (v % VPR) * 8;
             vec8_store<ST>(Ks + key * LDR + dc, kreg[p]);
-            if constexpr (sizeof(ST) == 2) {
-                *reinterpret_cast<uint4*>(Vs + (key * VPR + ((dc >> 3) ^ vt_swz<VPR>(key))) * 16) = vreg[p].v;
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) Vt[(dc + j) * LDT + key] = vec8_elem<ST>(vreg[p], j);
-            }
+            *reinterpret_cast<uint4*>(Vs + (key * VPR + ((dc >> 3) ^ vt_swz<VPR>(key))) * 16) = vreg[p].v;
         }
     };
 
@@ -243,32 +353,18 @@ __global__ __launch_bounds__(64 * NWV) void attn_fwd_tiled_kernel(const ST* __re
             const float pv[8] = {p[2 * u][0], p[2 * u][1], p[2 * u][2], p[2 * u][3],
                                  p[2 * u + 1][0], p[2 * u + 1][1], p[2 * u + 1][2], p[2 * u + 1][3]};
             const Frag8<ST> pf = frag8_from<ST>(pv);
-            if constexpr (sizeof(ST) == 2) {
-                // lane reads d columns 16 db + 4 (c16 % 4) .. + 3 at keys k0 and k0 + 16
-                u32x4 vt[DH / 16];
-                const int k0 = 32 * u + 4 * g + (c16 >> 2), k1 = k0 + 16;
+            // lane reads d columns 16 db + 4 (c16 % 4) .. + 3 at keys k0 and k0 + 16
+            Frag8<ST> vf[DH / 16];
+            const int k0 = 32 * u + 4 * g + (c16 >> 2), k1 = k0 + 16;
 #pragma unroll
-                for (int db = 0; db < DH / 16; ++db) {
-                    const int mcol = 16 * db + 4 * (c16 & 3), un = mcol >> 3, half = (mcol >> 2) & 1;
-                    const u32x2 lo = lds_read_tr16(Vs + (k0 * VPR + (un ^ vt_swz<VPR>(k0))) * 16 + 8 * half);
-                    const u32x2 hi = lds_read_tr16(Vs + (k1 * VPR + (un ^ vt_swz<VPR>(k1))) * 16 + 8 * half);
-                    vt[db] = u32x4{lo.x, lo.y, hi.x, hi.y};
-                }
-                lds_wait();
-#pragma unroll
-                for (int db = 0; db < DH / 16; ++db) {
-                    lds_ready(vt[db]);
-                    Frag8<ST> vf;
-                    vf.v = __builtin_bit_cast(bf16x8, vt[db]);
-                    mma8(o[db], vf, pf);
-                }
-            } else {
-#pragma unroll
-                for (int db = 0; db < DH / 16; ++db) {
-                    const ST* vrow = Vt + (db * 16 + c16) * LDT + 32 * u + 4 * g;
-                    mma8(o[db], frag8_from_quads<ST>(quad_load<ST>(vrow), quad_load<ST>(vrow + 16)), pf);
-                }
+            for (int db = 0; db < DH / 16; ++db) {
+                const int mcol = 16 * db + 4 * (c16 & 3), un = mcol >> 3, half = (mcol >> 2) & 1;
+                const u32x2 lo = lds_tr16(Vs + (k0 * VPR + (un ^ vt_swz<VPR>(k0))) * 16 + 8 * half);
+                const u32x2 hi = lds_tr16(Vs + (k1 * VPR + (un ^ vt_swz<VPR>(k1))) * 16 + 8 * half);
+                vf[db].v = __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
             }
+#pragma unroll
+            for (int db = 0; db < DH / 16; ++db) mma8(o[db], vf[db], pf);
         }
         mfma_drain();  // the loop may exit right here
     }
@@ -282,8 +378,7 @@ __global__ __launch_bounds__(64 * NWV) void attn_fwd_tiled_kernel(const ST* __re
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float x = o[db][i] * inv;
-            if constexpr (sizeof(ST) == 2) Os[c16 * LDR + db * 16 + 4 * g + i] = f32_to_bf16(x);
-            else Os[c16 * LDR + db * 16 + 4 * g + i] = x;
+            Os[c16 * LDR + db * 16 + 4 * g + i] = f32_to_bf16(x);
         }
     if (g == 0 && q < n) lse[(size_t)bh * n + q] = m_run * 0.69314718055994531f + logf(l_run);  // ln 2
     __syncthreads();
@@ -772,25 +867,35 @@ int launch_attn_fwd_t(const ST* QKV, const float* r, int BH, int n, int dh, int 
             return hipGetLastError() == hipSuccess ? 0 : -1;
         }
     }
-    if (n > 32 || window > 0) {
-        // bf16 with 64-wide heads: 128 queries (8 waves) per workgroup share each K/V tile
-        constexpr int W64 = sizeof(ST) == 2 ? 8 : 4;
-        auto kern = window > 0 ? (dh == 64 ? attn_fwd_tiled_kernel<ST, 64, true, W64>
-                                           : attn_fwd_tiled_kernel<ST, 32, true, 4>)
-                               : (dh == 64 ? attn_fwd_tiled_kernel<ST, 64, false, W64>
-                                           : attn_fwd_tiled_kernel<ST, 32, false, 4>);
-        const int qbw = 16 * (dh == 64 ? W64 : 4);
-        const dim3 grid(BH * ((n + qbw - 1) / qbw)), block(4 * qbw);
-        hipLaunchKernelGGL(kern, grid, block, 0, stream, QKV, BH, n, causal, lb, scale, r, A, lse);
+    if constexpr (sizeof(ST) == 4) {
+        // up to 8 waves per block of 16 queries (fewer when the head has fewer blocks to share out)
+        const int nqb = (n + 15) / 16;
+        int nw = 1;
+        while (nw < kAttnF32MaxWaves && 2 * nw <= nqb) nw *= 2;
+        auto kern = window > 0 ? (dh == 64 ? attn_fwd_f32_kernel<64, true> : attn_fwd_f32_kernel<32, true>)
+                               : (dh == 64 ? attn_fwd_f32_kernel<64, false> : attn_fwd_f32_kernel<32, false>);
+        const size_t lds = dh == 64 ? AttnF32<64>::lds(nw) : AttnF32<32>::lds(nw);
+        hipLaunchKernelGGL(kern, dim3(BH * nqb), dim3(64 * nw), lds, stream, QKV, BH, n, causal, lb, scale, r, A, lse);
+        return hipGetLastError() == hipSuccess ? 0 : -1;
+    } else {
+        if (n > 32 || window > 0) {
+            // 32-wide heads past the LDS kernel's rows or with a window (64-wide
+            // ones take the flash kernel above)
+            constexpr int NWV = 4;
+            if (dh != 32) return -1;
+            auto kern = window > 0 ? attn_fwd_tiled_kernel<ST, 32, true, NWV> : attn_fwd_tiled_kernel<ST, 32, false, NWV>;
+            const dim3 grid(BH * ((n + 16 * NWV - 1) / (16 * NWV))), block(64 * NWV);
+            hipLaunchKernelGGL(kern, grid, block, 0, stream, QKV, BH, n, causal, lb, scale, r, A, lse);
+            return hipGetLastError() == hipSuccess ? 0 : -1;
+        }
+        const int tasks = BH * ((n + 15) / 16);
+        dim3 grid((tasks + 3) / 4), block(256);
+        if (dh == 64)
+            hipLaunchKernelGGL((attn_fwd_kernel<ST, 64>), grid, block, 0, stream, QKV, BH, n, causal, scale, r, A, lse);
+        else
+            hipLaunchKernelGGL((attn_fwd_kernel<ST, 32>), grid, block, 0, stream, QKV, BH, n, causal, scale, r, A, lse);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
-    const int tasks = BH * ((n + 15) / 16);
-    dim3 grid((tasks + 3) / 4), block(256);
-    if (dh == 64)
-        hipLaunchKernelGGL((attn_fwd_kernel<ST, 64>), grid, block, 0, stream, QKV, BH, n, causal, scale, r, A, lse);
-    else
-        hipLaunchKernelGGL((attn_fwd_kernel<ST, 32>), grid, block, 0, stream, QKV, BH, n, causal, scale, r, A, lse);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 }  // namespace

@@ -7,35 +7,50 @@
 //   dK_j  = sum_i dS_ij Q_i / sqrt(dh),  dQ_i = sum_j dS_ij K_j / sqrt(dh)
 // Two passes so that no value is ever accumulated by atomics (results are
 // bitwise reproducible):
-//   kv pass: one wave per block of 16 keys, loop over the query blocks that
+//   kv pass: per block of 16 keys, loop over the query blocks that
 //            may attend to them; S and dP tiles come out with the key in the
 //            lane (lane % 16) and queries in rows, i.e. already in the K = 16
 //            operand layout for dV^T += dA^T P and dK^T += Q^T dS;
-//   q pass:  one wave per block of 16 queries, loop over allowed key blocks;
+//   q pass:  per block of 16 queries, loop over allowed key blocks;
 //            S^T and dP^T tiles (query in the lane) feed dQ^T += K^T dS^T.
 #include "common.h"
 #include "gemm2.h"
 #include "kernels.h"
 #include "rope.h"
-#include "tiles.h"
 
 namespace mosa {
 
 namespace {
 
-template <typename ST, int DH, bool WIN>
-__global__ __launch_bounds__(256) void attn_bwd_kv_kernel(const ST* __restrict__ QKV, const ST* __restrict__ dA,
-                                                          const float* __restrict__ lse, const float* __restrict__ D,
-                                                          int BH, int n, int causal, int lb, float scale,
-                                                          ST* __restrict__ dQKV, const int32_t* __restrict__ rI,
-                                                          const float2* __restrict__ rtab) {
-    constexpr int RS = 3 * DH;  // row stride of the packed Q | K | V (and dQ | dK | dV) rows
+// fp32 storage: one workgroup of NW waves per (b, h), pass and block of 16 keys
+// (kv pass, blocks [0, BH nb)) or 16 queries (q pass, the rest).  The waves take
+// the blocks of the other side in turn (wave w the blocks w, w + NW, ...) from
+// global memory and their partial sums are added in wave order through LDS
+// (reproducible).  Such heads are few and short, so the kernel is bound by the
+// latency of its block loop (about 3 us a block) and by how much of the chip
+// it fills: with one wave walking all blocks of its 16 rows, 4 heads of 512
+// rows took 112 us (kv) + 70 us (q) on 32 workgroups per pass; as here both
+// take 21 us on 256 (2 heads of 4096 rows, the whole training step: 1639 ->
+// 531 us).
+constexpr int kBwdF32MaxWaves = 8;
+
+template <int DH>
+struct BwdF32 {
+    static constexpr int NDB = DH / 16;
+    // one wave's partial dK^T and dV^T (or dQ^T) blocks, one float4 per lane each
+    static constexpr size_t lds(int nw) { return (size_t)nw * 2 * NDB * 64 * sizeof(float4); }
+};
+
+template <int DH, bool WIN>
+__device__ __forceinline__ void attn_bwd_f32_kv(float4* part, int nw, int bh, int j0, const float* __restrict__ QKV,
+                                                const float* __restrict__ dA, const float* __restrict__ lse,
+                                                const float* __restrict__ D, int n, int causal, int lb, float scale,
+                                                float* __restrict__ dQKV, const int32_t* __restrict__ rI,
+                                                const float2* __restrict__ rtab) {
+    using ST = float;
+    constexpr int RS = 3 * DH, NDB = DH / 16;  // row stride of the packed rows
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane >> 4, c16 = lane & 15;
-    const int nb = (n + 15) / 16;
-    const int task = blockIdx.x * 4 + wave;
-    if (task >= BH * nb) return;
-    const int bh = task / nb, j0 = (task % nb) * 16;
     const size_t base = (size_t)bh * n;
     const ST* Qp = QKV + base * RS;
     const ST* Kp = Qp + DH;
@@ -49,13 +64,13 @@ __global__ __launch_bounds__(256) void attn_bwd_kv_kernel(const ST* __restrict__
         kf[s] = key < n ? frag8_load<ST>(Kp + (size_t)key * RS + s * 32 + 8 * g) : frag8_zero<ST>();
         vf[s] = key < n ? frag8_load<ST>(Vp + (size_t)key * RS + s * 32 + 8 * g) : frag8_zero<ST>();
     }
-    f32x4 dKt[DH / 16], dVt[DH / 16];
+    f32x4 dKt[NDB], dVt[NDB];
 #pragma unroll
-    for (int db = 0; db < DH / 16; ++db) dKt[db] = dVt[db] = zero4();
+    for (int db = 0; db < NDB; ++db) dKt[db] = dVt[db] = zero4();
 
     // causal with a window: queries up to lb past the block's last key see it
     const int i_end = WIN && causal ? min(n, j0 + 16 + lb) : n;
-    for (int i0 = causal ? j0 : 0; i0 < i_end; i0 += 16) {
+    for (int i0 = (causal ? j0 : 0) + 16 * wave; i0 < i_end; i0 += 16 * nw) {
         const int qa = i0 + c16;  // query this lane feeds as MFMA A row
         f32x4 s = zero4(), dp = zero4();
 #pragma unroll
@@ -79,48 +94,55 @@ __global__ __launch_bounds__(256) void attn_bwd_kv_kernel(const ST* __restrict__
         const Frag4<ST> pf = frag4_from<ST>(p);
         const Frag4<ST> dsf = frag4_from<ST>(ds);
 #pragma unroll
-        for (int db = 0; db < DH / 16; ++db) {
+        for (int db = 0; db < NDB; ++db) {
             float at[4], qt[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int q = i0 + 4 * g + i;
-                at[i] = q < n ? ld1<ST>(dAp + (size_t)q * DH + db * 16 + c16) : 0.f;
-                qt[i] = q < n ? ld1<ST>(Qp + (size_t)q * RS + db * 16 + c16) : 0.f;
+                at[i] = q < n ? dAp[(size_t)q * DH + db * 16 + c16] : 0.f;
+                qt[i] = q < n ? Qp[(size_t)q * RS + db * 16 + c16] : 0.f;
             }
             mma4(dVt[db], frag4_from<ST>(at), pf);
             mma4(dKt[db], frag4_from<ST>(qt), dsf);
         }
         mfma_drain();  // the loop may exit right here
     }
-    if (key < n) {
-        // lane: key column c16, d_head rows db*16 + 4g + i
-        const int pos = rtab ? (rI ? rI[base + key] : key) : 0;
 #pragma unroll
-        for (int db = 0; db < DH / 16; ++db) {
-            float x[4] = {dKt[db][0] * scale, dKt[db][1] * scale, dKt[db][2] * scale, dKt[db][3] * scale};
-            if (rtab) rope4_back<DH>(x, db * 16 + 4 * g, rtab, pos);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                st1<ST>(dQKV + (base + key) * RS + 2 * DH + db * 16 + 4 * g + i, dVt[db][i]);
-                st1<ST>(dQKV + (base + key) * RS + DH + db * 16 + 4 * g + i, x[i]);
-            }
+    for (int db = 0; db < NDB; ++db) {
+        part[(wave * 2 * NDB + db) * 64 + lane] = make_float4(dKt[db][0], dKt[db][1], dKt[db][2], dKt[db][3]);
+        part[(wave * 2 * NDB + NDB + db) * 64 + lane] = make_float4(dVt[db][0], dVt[db][1], dVt[db][2], dVt[db][3]);
+    }
+    __syncthreads();
+    // item (dK or dV, db) by a wave: lane's key column c16, d_head rows db*16 + 4g + i
+    if (key >= n) return;
+    const int pos = rtab ? (rI ? rI[base + key] : key) : 0;
+    for (int it = wave; it < 2 * NDB; it += nw) {
+        float x[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < nw; ++w) {
+            const float4 v = part[(w * 2 * NDB + it) * 64 + lane];
+            x[0] += v.x; x[1] += v.y; x[2] += v.z; x[3] += v.w;
         }
+        const int d0 = (it % NDB) * 16 + 4 * g;
+        if (it < NDB) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] *= scale;
+            if (rtab) rope4_back<DH>(x, d0, rtab, pos);
+        }
+        *reinterpret_cast<float4*>(dQKV + (base + key) * RS + (it < NDB ? DH : 2 * DH) + d0) =
+            make_float4(x[0], x[1], x[2], x[3]);
     }
 }
 
-template <typename ST, int DH, bool WIN>
-__global__ __launch_bounds__(256) void attn_bwd_q_kernel(const ST* __restrict__ QKV, const ST* __restrict__ dA,
-                                                         const float* __restrict__ lse, const float* __restrict__ D,
-                                                         int BH, int n, int causal, int lb, float scale,
-                                                         ST* __restrict__ dQKV, const int32_t* __restrict__ rI,
-                                                         const float2* __restrict__ rtab) {
-    constexpr int RS = 3 * DH;
+template <int DH, bool WIN>
+__device__ __forceinline__ void attn_bwd_f32_q(float4* part, int nw, int bh, int i0, const float* __restrict__ QKV,
+                                               const float* __restrict__ dA, const float* __restrict__ lse,
+                                               const float* __restrict__ D, int n, int causal, int lb, float scale,
+                                               float* __restrict__ dQKV, const int32_t* __restrict__ rI,
+                                               const float2* __restrict__ rtab) {
+    using ST = float;
+    constexpr int RS = 3 * DH, NDB = DH / 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane >> 4, c16 = lane & 15;
-    const int nb = (n + 15) / 16;
-    const int task = blockIdx.x * 4 + wave;
-    if (task >= BH * nb) return;
-    const int bh = task / nb, i0 = (task % nb) * 16;
     const size_t base = (size_t)bh * n;
     const ST* Qp = QKV + base * RS;
     const ST* Kp = Qp + DH;
@@ -136,12 +158,12 @@ __global__ __launch_bounds__(256) void attn_bwd_q_kernel(const ST* __restrict__ 
     }
     const float lq = q < n ? lse[base + q] : 0.f;
     const float dq = q < n ? D[base + q] : 0.f;
-    f32x4 dQt[DH / 16];
+    f32x4 dQt[NDB];
 #pragma unroll
-    for (int db = 0; db < DH / 16; ++db) dQt[db] = zero4();
+    for (int db = 0; db < NDB; ++db) dQt[db] = zero4();
 
     const int kv_end = causal ? min(n, i0 + 16) : n;
-    for (int j0 = WIN && causal ? max(0, i0 - lb) / 16 * 16 : 0; j0 < kv_end; j0 += 16) {
+    for (int j0 = (WIN && causal ? max(0, i0 - lb) / 16 * 16 : 0) + 16 * wave; j0 < kv_end; j0 += 16 * nw) {
         const int kr = j0 + c16;
         f32x4 s = zero4(), dp = zero4();
 #pragma unroll
@@ -162,26 +184,52 @@ __global__ __launch_bounds__(256) void attn_bwd_q_kernel(const ST* __restrict__ 
         }
         const Frag4<ST> dsf = frag4_from<ST>(ds);
 #pragma unroll
-        for (int db = 0; db < DH / 16; ++db) {
+        for (int db = 0; db < NDB; ++db) {
             float kt[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int j = j0 + 4 * g + i;
-                kt[i] = j < n ? ld1<ST>(Kp + (size_t)j * RS + db * 16 + c16) : 0.f;
+                kt[i] = j < n ? Kp[(size_t)j * RS + db * 16 + c16] : 0.f;
             }
             mma4(dQt[db], frag4_from<ST>(kt), dsf);
         }
         mfma_drain();  // the loop may exit right here
     }
-    if (q < n) {
-        const int pos = rtab ? (rI ? rI[base + q] : q) : 0;
 #pragma unroll
-        for (int db = 0; db < DH / 16; ++db) {
-            float x[4] = {dQt[db][0] * scale, dQt[db][1] * scale, dQt[db][2] * scale, dQt[db][3] * scale};
-            if (rtab) rope4_back<DH>(x, db * 16 + 4 * g, rtab, pos);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) st1<ST>(dQKV + (base + q) * RS + db * 16 + 4 * g + i, x[i]);
+    for (int db = 0; db < NDB; ++db)
+        part[(wave * NDB + db) * 64 + lane] = make_float4(dQt[db][0], dQt[db][1], dQt[db][2], dQt[db][3]);
+    __syncthreads();
+    if (q >= n) return;
+    const int pos = rtab ? (rI ? rI[base + q] : q) : 0;
+    for (int db = wave; db < NDB; db += nw) {
+        float x[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < nw; ++w) {
+            const float4 v = part[(w * NDB + db) * 64 + lane];
+            x[0] += v.x; x[1] += v.y; x[2] += v.z; x[3] += v.w;
         }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] *= scale;
+        if (rtab) rope4_back<DH>(x, db * 16 + 4 * g, rtab, pos);
+        *reinterpret_cast<float4*>(dQKV + (base + q) * RS + db * 16 + 4 * g) = make_float4(x[0], x[1], x[2], x[3]);
+    }
+}
+
+template <int DH, bool WIN>
+__global__ __launch_bounds__(64 * kBwdF32MaxWaves) void attn_bwd_f32_kernel(
+    const float* __restrict__ QKV, const float* __restrict__ dA, const float* __restrict__ lse,
+    const float* __restrict__ D, int BH, int n, int causal, int lb, float scale, float* __restrict__ dQKV,
+    const int32_t* __restrict__ rI, const float2* __restrict__ rtab) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    float4* part = reinterpret_cast<float4*>(smem);
+    const int nb = (n + 15) / 16, nw = blockDim.x >> 6;
+    // even blocks one pass, odd ones the other, each with the blocks that have
+    // the most work first (causal: low keys, high queries)
+    const int b = blockIdx.x, task = b >> 1, bh = task % BH, blk = task / BH;
+    if (b & 1) {
+        attn_bwd_f32_q<DH, WIN>(part, nw, bh, 16 * (causal ? nb - 1 - blk : blk), QKV, dA, lse, D, n, causal, lb, scale,
+                                dQKV, rI, rtab);
+    } else {
+        attn_bwd_f32_kv<DH, WIN>(part, nw, bh, 16 * blk, QKV, dA, lse, D, n, causal, lb, scale, dQKV, rI, rtab);
     }
 }
 
@@ -1012,23 +1060,21 @@ __global__ __launch_bounds__(256) void attn_bwd_small_kernel(const uint16_t* __r
     }
 }
 
-template <typename ST>
-int launch_t(const ST* QKV, const ST* dA, const float* lse, const float* D, int BH, int n, int dh, int causal,
-             int window, ST* dQKV, const int32_t* rI, const float2* rtab, int pass, hipStream_t stream) {
+// bf16 storage: one launch for both passes (the one-wave kernel for n <= 16, the
+// LDS kernels up to their limit, the tiled kernels beyond and with a window).
+int launch_bf16(const uint16_t* QKV, const uint16_t* dA, const float* lse, const float* D, int BH, int n, int dh,
+                int causal, int window, uint16_t* dQKV, const int32_t* rI, const float2* rtab, hipStream_t stream) {
+    using ST = uint16_t;
+    if (BH == 0) return 0;
     const float scale = 1.0f / sqrtf((float)dh);
     const int lb = window > 0 ? window - 1 : n;  // keys a query may look back
-    if constexpr (sizeof(ST) == 2) {
-      if (n <= 16 && window == 0 && (dh == 64 || dh == 32)) {
-        // both passes in one launch: the call for the dQ pass has nothing left to do
-        if (pass == 1 || BH == 0) return 0;
+    if (n <= 16 && window == 0 && (dh == 64 || dh == 32)) {
         auto kern = dh == 64 ? attn_bwd_small_kernel<64> : attn_bwd_small_kernel<32>;
         hipLaunchKernelGGL(kern, dim3((BH + 3) / 4), dim3(256), 0, stream, QKV, dA, lse, D, BH, n, causal, scale,
                            dQKV, rI, rtab);
         return hipGetLastError() == hipSuccess ? 0 : -1;
-      }
-      if (n <= kAttnBwdLdsMaxN && window == 0) {
-        // both passes in one launch: the call for the dQ pass has nothing left to do
-        if (pass == 1) return 0;
+    }
+    if (n <= kAttnBwdLdsMaxN && window == 0) {
         auto go = [&](auto dht, auto nmt) {
             constexpr int DH = decltype(dht)::value, NM = decltype(nmt)::value;
             auto kern = attn_bwd_lds_kernel<DH, NM>;
@@ -1044,15 +1090,13 @@ int launch_t(const ST* QKV, const ST* dA, const float* lse, const float* D, int 
             return go(dht, std::integral_constant<int, 128>{});
         };
         return dh == 64 ? size(std::integral_constant<int, 64>{}) : size(std::integral_constant<int, 32>{});
-      }
-      {
-        // 4 waves per workgroup, 16 CB owned rows per wave.  Two column
-        // blocks (half the LDS reads per MFMA, 2 waves per SIMD) where the
-        // rows are long (n >= 1024, no window) and the blocks still give
-        // every CU two workgroups (4 dense heads, B = 8, T = 1024: 44 -> 39.5 us); one
-        // otherwise (measured slower with two: n = 512 MoSA heads, local
-        // windows, a single head of T = 8192 that fills half the chip).
-        if (pass != 2) return -1;  // both passes are one launch here
+    }
+    // 4 waves per workgroup, 16 CB owned rows per wave.  Two column
+    // blocks (half the LDS reads per MFMA, 2 waves per SIMD) where the
+    // rows are long (n >= 1024, no window) and the blocks still give
+    // every CU two workgroups (4 dense heads, B = 8, T = 1024: 44 -> 39.5 us); one
+    // otherwise (measured slower with two: n = 512 MoSA heads, local
+    // windows, a single head of T = 8192 that fills half the chip).
 #define MOSA_ATTN_BWD_T(DHV, CBV)                                                                      \
     do {                                                                                                \
         constexpr int NWV = 4, CB = CBV, OB = 16 * CB * NWV;                                            \
@@ -1066,61 +1110,42 @@ int launch_t(const ST* QKV, const ST* dA, const float* lse, const float* D, int 
         if (dh == 64) MOSA_ATTN_BWD_T(64, CBV);                                                         \
         else MOSA_ATTN_BWD_T(32, CBV);                                                                  \
     } while (0)
-        const bool wide = window == 0 && n >= 1024 && 2LL * BH * ((n + 127) / 128) >= 512;
-        if (wide) MOSA_ATTN_BWD_TD(2);
-        else MOSA_ATTN_BWD_TD(1);
+    const bool wide = window == 0 && n >= 1024 && 2LL * BH * ((n + 127) / 128) >= 512;
+    if (wide) MOSA_ATTN_BWD_TD(2);
+    else MOSA_ATTN_BWD_TD(1);
 #undef MOSA_ATTN_BWD_TD
 #undef MOSA_ATTN_BWD_T
-        return hipGetLastError() == hipSuccess ? 0 : -1;
-      }
-    } else {
-      if (pass == 2)
-          return launch_t<ST>(QKV, dA, lse, D, BH, n, dh, causal, window, dQKV, rI, rtab, 0, stream) |
-                 launch_t<ST>(QKV, dA, lse, D, BH, n, dh, causal, window, dQKV, rI, rtab, 1, stream);
-      const int tasks = BH * ((n + 15) / 16);
-      dim3 grid((tasks + 3) / 4), block(256);
-#define MOSA_ATTN_BWD(KERN, DHV)                                                                     \
-      do {                                                                                              \
-          auto kern = window > 0 ? KERN<ST, DHV, true> : KERN<ST, DHV, false>;                          \
-          hipLaunchKernelGGL(kern, grid, block, 0, stream, QKV, dA, lse, D, BH, n, causal, lb, scale, dQKV, rI, rtab); \
-      } while (0)
-      if (pass == 0) {
-          if (dh == 64) MOSA_ATTN_BWD(attn_bwd_kv_kernel, 64);
-          else MOSA_ATTN_BWD(attn_bwd_kv_kernel, 32);
-      } else {
-          if (dh == 64) MOSA_ATTN_BWD(attn_bwd_q_kernel, 64);
-          else MOSA_ATTN_BWD(attn_bwd_q_kernel, 32);
-      }
-#undef MOSA_ATTN_BWD
-      return hipGetLastError() == hipSuccess ? 0 : -1;
-    }
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// fp32 storage: both passes in one launch, up to 8 waves per block of 16 rows
+// (fewer when the head has fewer blocks to share out).
+int launch_f32(const float* QKV, const float* dA, const float* lse, const float* D, int BH, int n, int dh, int causal,
+               int window, float* dQKV, const int32_t* rI, const float2* rtab, hipStream_t stream) {
+    if (BH == 0) return 0;
+    const float scale = 1.0f / sqrtf((float)dh);
+    const int lb = window > 0 ? window - 1 : n, nb = (n + 15) / 16;
+    int nw = 1;
+    while (nw < kBwdF32MaxWaves && 2 * nw <= nb) nw *= 2;
+    auto kern = window > 0 ? (dh == 64 ? attn_bwd_f32_kernel<64, true> : attn_bwd_f32_kernel<32, true>)
+                           : (dh == 64 ? attn_bwd_f32_kernel<64, false> : attn_bwd_f32_kernel<32, false>);
+    const size_t lds = dh == 64 ? BwdF32<64>::lds(nw) : BwdF32<32>::lds(nw);
+    static_assert(BwdF32<64>::lds(kBwdF32MaxWaves) <= 64 * 1024, "default LDS limit");
+    hipLaunchKernelGGL(kern, dim3(2 * BH * nb), dim3(64 * nw), lds, stream, QKV, dA, lse, D, BH, n, causal, lb, scale,
+                       dQKV, rI, rtab);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 }  // namespace
 
-// One launch for both passes where a kernel does both (bf16: the one-wave
-// kernel for n <= 16, the LDS kernels up to their limit, the tiled kernels
-// beyond and with a window), else the two passes (fp32).
 int launch_attn_bwd(int dtype, const void* QKV, const void* dA, const float* lse, const float* D, int BH, int n,
                     int dh, int causal, int window, void* dQKV, const int32_t* rope_I, const float2* rope,
                     int dense, const Marker& mk, hipStream_t stream) {
-    auto run = [&](auto tag, int pass) {
-        using ST = decltype(tag);
-        return launch_t<ST>((const ST*)QKV, (const ST*)dA, lse, D, BH, n, dh, causal, window, (ST*)dQKV, rope_I,
-                            rope, pass, stream);
-    };
-    auto go = [&](auto tag) {
-        using ST = decltype(tag);
-        if constexpr (sizeof(ST) == 2) {
-            const int e = run(tag, 2);
-            return e | mk(dense ? "attn_bwd_dense" : "attn_bwd");
-        }
-        int e = run(tag, 0);
-        e |= mk(dense ? "attn_bwd_kv_dense" : "attn_bwd_kv");
-        e |= run(tag, 1);
-        return e | mk(dense ? "attn_bwd_q_dense" : "attn_bwd_q");
-    };
-    return dtype == kBF16 ? go(uint16_t{}) : go(float{});
+    const int e = dtype == kBF16 ? launch_bf16((const uint16_t*)QKV, (const uint16_t*)dA, lse, D, BH, n, dh, causal,
+                                               window, (uint16_t*)dQKV, rope_I, rope, stream)
+                                 : launch_f32((const float*)QKV, (const float*)dA, lse, D, BH, n, dh, causal, window,
+                                              (float*)dQKV, rope_I, rope, stream);
+    return e | mk(dense ? "attn_bwd_dense" : "attn_bwd");
 }
 
 }  // namespace mosa

@@ -92,10 +92,8 @@ int launch_dattn_out(int dtype, const void* dY, const int32_t* I, const float* r
                      const void* A, int B, int T, int d, int H, int dh, int n, void* dA, float* D, float* dz,
                      void* dz16, hipStream_t stream);
 
-// Attention backward into packed dQKV rows (dQ, dK and dV; one launch where
-// the kernels allow it).  Marks "attn_bwd" (dense heads: "attn_bwd_dense"),
-// or "attn_bwd_kv" and "attn_bwd_q" (+ "_dense") when the passes are two
-// launches.
+// Attention backward into packed dQKV rows (dQ, dK and dV in one launch).
+// Marks "attn_bwd" (dense heads: "attn_bwd_dense").
 int launch_attn_bwd(int dtype, const void* QKV, const void* dA, const float* lse, const float* D, int BH,
                     int n, int dh, int causal, int window, void* dQKV, const int32_t* rope_I,
                     const float2* rope, int dense, const Marker& mk, hipStream_t stream);
