@@ -24,9 +24,11 @@ namespace mosa {
 
 namespace {
 
-template <typename ST, int DH>
+// SMALL (fp32): 16 (64-wide heads) or 32 rows per workgroup instead of 64.
+template <typename ST, int DH, bool SMALL = false>
 struct BwdOutPolicy {
-    static constexpr int MT = 64, NT = DH, KC = sizeof(ST) == 2 ? 64 : 32, WM = 4, WN = 1;
+    static constexpr int MT = !SMALL ? 64 : DH == 64 ? 16 : 32, NT = DH, KC = sizeof(ST) == 2 ? 64 : 32;
+    static constexpr int WM = MT == 64 ? 4 : MT / 16, WN = 4 / WM;
     static constexpr size_t EPI_LDS = 0;
     static constexpr bool A_KCONTIG = true, B_KCONTIG = true, A_SCALED = false;
     struct Args {
@@ -86,7 +88,7 @@ struct BwdOutPolicy {
         constexpr int CW = DH / 4;
         const int ml = tid >> 2, cq = (tid & 3) * CW;
         const int m = m0 + ml;
-        const bool ok = m < a.M;
+        const bool ok = ml < MT && m < a.M;
         size_t ri = 0;
         float c[CW], part = 0.f;
         if (ok) {
@@ -158,13 +160,21 @@ struct BwdOutPolicy2 {
 template <typename ST, int DH>
 int run(const ST* dY, const int32_t* I, const float* r, const ST* Wo, const ST* A, int B, int T, int d, int H, int n,
         ST* dA, float* D, float* dz, ST* dz16, hipStream_t stream) {
-    using P = BwdOutPolicy<ST, DH>;
     const int M = B * n;
-    typename P::Args a{dY, I, r, Wo, A, dA, D, dz, dz16, T, d, H, n, M, (M + P::MT - 1) / P::MT};
-    if constexpr (sizeof(ST) == 2) {
-        if (d % BwdOutPolicy2<DH>::KC == 0) return launch_gemm2<BwdOutPolicy2<DH>>(a, H * a.mtiles, stream);
+    auto args = [&](auto p) {
+        using P = decltype(p);
+        return typename P::Args{dY, I, r, Wo, A, dA, D, dz, dz16, T, d, H, n, M, (M + P::MT - 1) / P::MT};
+    };
+    if constexpr (sizeof(ST) == 2) {  // d is a multiple of 64 = KC
+        const auto a = args(BwdOutPolicy<ST, DH>{});
+        return launch_gemm2<BwdOutPolicy2<DH>>(a, H * a.mtiles, stream);
+    } else {
+        auto go = [&](auto p) {
+            const auto a = args(p);
+            return launch_gemm<ST, decltype(p)>(a, H * a.mtiles, stream);
+        };
+        return (M + 63) / 64 * H < kFullChip ? go(BwdOutPolicy<ST, DH, true>{}) : go(BwdOutPolicy<ST, DH>{});
     }
-    return launch_gemm<ST, P>(a, H * a.mtiles, stream);
 }
 
 }  // namespace

@@ -22,9 +22,9 @@ namespace mosa {
 
 namespace {
 
-template <typename ST, int DH>
+template <typename ST, int DH, bool SMALL = false>
 struct DxProjPolicy {
-    static constexpr int MT = 64, NT = 128, KC = (sizeof(ST) == 2 && DH == 64) ? 64 : 32, WM = 2, WN = 2;
+    static constexpr int MT = SMALL ? 32 : 64, NT = SMALL ? 64 : 128, KC = (sizeof(ST) == 2 && DH == 64) ? 64 : 32, WM = 2, WN = 2;
     static constexpr size_t EPI_LDS = 0;
     static constexpr bool A_KCONTIG = true, B_KCONTIG = true, A_SCALED = false;
     struct Args {
@@ -94,9 +94,9 @@ struct DxProjPolicy {
     }
 };
 
-template <typename ST, int DH>
+template <typename ST, int DH, bool SMALL = false>
 struct DxCombinePolicy {
-    static constexpr int MT = 64, NT = 128, KC = 32, WM = 2, WN = 2;
+    static constexpr int MT = SMALL ? 32 : 64, NT = SMALL ? 64 : 128, KC = 32, WM = 2, WN = 2;
     static constexpr size_t EPI_LDS = kCombineLds;
     static constexpr bool A_KCONTIG = true, B_KCONTIG = true, A_SCALED = false;
     struct Args {
@@ -158,9 +158,9 @@ struct DxCombinePolicy {
 
 // The dense heads' part alone ([B, T, d] in the storage type, here fp32) for
 // combine_rows_kernel to start from.
-template <typename ST, int DH>
-struct DxDensePolicy : DxCombinePolicy<ST, DH> {
-    using Base = DxCombinePolicy<ST, DH>;
+template <typename ST, int DH, bool SMALL>
+struct DxDensePolicy : DxCombinePolicy<ST, DH, SMALL> {
+    using Base = DxCombinePolicy<ST, DH, SMALL>;
     static constexpr size_t EPI_LDS = 0;
     struct Args : Base::Args {
         float* base;
@@ -239,7 +239,6 @@ struct DxDensePolicy2 {
 template <typename ST, int DH>
 int run_proj(const ST* dQKV, const float* dz, const ST* Wq, const ST* Wk, const ST* Wv, const ST* Wr, int B, int d,
              int H, int k, ST* dXs, hipStream_t stream) {
-    using P = DxProjPolicy<ST, DH>;
     const int M = B * k;
     if constexpr (sizeof(ST) == 2) {
         using R = DxProjRowPolicy<DH>;
@@ -248,8 +247,15 @@ int run_proj(const ST* dQKV, const float* dz, const ST* Wq, const ST* Wk, const 
         if (dx_row_args<DH>(dQKV, dz, Wq, Wk, Wv, Wr, B, d, H, k, dXs, ra, nblocks))
             return launch_rowgemm<R>(ra, nblocks, stream);
     }
-    typename P::Args a{dQKV, dz, Wq, Wk, Wv, Wr, dXs, d, H, k, M, (M + P::MT - 1) / P::MT, (d + P::NT - 1) / P::NT};
-    return launch_gemm<ST, P>(a, H * a.mtiles * a.ntiles, stream);
+    auto go = [&](auto small) {
+        using P = DxProjPolicy<ST, DH, decltype(small)::value>;
+        typename P::Args a{dQKV, dz, Wq, Wk, Wv, Wr, dXs, d, H, k, M, (M + P::MT - 1) / P::MT, (d + P::NT - 1) / P::NT};
+        return launch_gemm<ST, P>(a, H * a.mtiles * a.ntiles, stream);
+    };
+    if constexpr (sizeof(ST) == 4) {
+        if ((M + 63) / 64 * ((d + 127) / 128) * H < kFullChip) return go(std::true_type{});
+    }
+    return go(std::false_type{});
 }
 
 template <typename ST, int DH>
@@ -273,11 +279,16 @@ int run_combine(const ST* dQKVd, const ST* Wq, const ST* Wk, const ST* Wv, const
                                      mt, nt};
                 e = launch_gemm2<P2>(a2, B * mt * nt, stream);
             } else {
-                using PD = DxDensePolicy<ST, DH>;
-                typename PD::Args ad{};
-                static_cast<typename P::Args&>(ad) = a;
-                ad.base = base;
-                e = launch_gemm<ST, PD>(ad, B * a.mtiles * a.ntiles, stream);
+                auto go = [&](auto small) {
+                    using PD = DxDensePolicy<ST, DH, decltype(small)::value>;
+                    const int mt = (T + PD::MT - 1) / PD::MT, nt = (d + PD::NT - 1) / PD::NT;
+                    typename PD::Args ad{};
+                    static_cast<typename PD::Base::Args&>(ad) = {dQKVd, Wq, Wk, Wv, slot, dXs, dX, T, d, H, k, Hd,
+                                                                 accumulate, mt, nt};
+                    ad.base = base;
+                    return launch_gemm<ST, PD>(ad, B * mt * nt, stream);
+                };
+                e = B * a.mtiles * a.ntiles < kFullChip ? go(std::true_type{}) : go(std::false_type{});
             }
             if (e | mk("dx_dense")) return -1;
         }

@@ -16,10 +16,12 @@
 //                LDS so that the data loads of a chunk depend on LDS only;
 //                a_kaddr(info, m8) / b_kaddr(info, n8) give an address of 8
 //                consecutive elements that is always safe to load (clamped),
-//                a_kok / b_kok whether they are real (else zeros) and
-//                a_kscale(info) an optional scale.
-//                The engine transposes 8x8 blocks in registers so that LDS
-//                stores stay 16-byte wide.
+//                a_kok / b_kok whether they are real (else zeros).
+//                bf16: the engine transposes 8x8 blocks in registers so that LDS
+//                stores stay 16-byte wide.  fp32: the tile stays as in memory,
+//                [k][m], every thread moves 4 consecutive m (an 8x8 block per
+//                thread kept 32 of 256 threads busy on a 64 x 32 tile), and
+//                the MFMA operands, one float per lane and k, are read from there.
 // a_fallback / b_fallback give a valid address that is loaded (and then
 // zeroed) in place of out-of-range k-contiguous vectors, so that every load of
 // a chunk is issued without a branch and waited for only at the commit.
@@ -143,12 +145,21 @@ struct GemmShape {
     static constexpr int B_BLKS = (NT / 8) * (KC / 8);
     static constexpr int A_PER = P::A_KCONTIG ? (A_VECS + 255) / 256 : (A_BLKS + 255) / 256;
     static constexpr int B_PER = P::B_KCONTIG ? (B_VECS + 255) / 256 : (B_BLKS + 255) / 256;
+    // fp32 m-contiguous tiles: rows of k, 4 floats per unit
+    static constexpr int LDA_M = MT + 4, LDB_M = NT + 4;
+    static constexpr int A_U4 = KC * MT / 4, B_U4 = KC * NT / 4;
+    static constexpr int A_PER4 = (A_U4 + 255) / 256, B_PER4 = (B_U4 + 255) / 256;
+    template <typename ST> static constexpr bool a_rows() { return sizeof(ST) == 4 && !P::A_KCONTIG; }
+    template <typename ST> static constexpr bool b_rows() { return sizeof(ST) == 4 && !P::B_KCONTIG; }
+    // elements of one operand buffer
+    template <typename ST> static constexpr int a_elems() { return a_rows<ST>() ? KC * LDA_M : MT * LDK; }
+    template <typename ST> static constexpr int b_elems() { return b_rows<ST>() ? KC * LDB_M : NT * LDK; }
     static_assert(WM * WN == 4, "4 waves");
     static_assert(WTM % 16 == 0 && WTN % 16 == 0 && KC % 32 == 0, "tile shape");
     static constexpr bool ROWS = !P::A_KCONTIG || !P::B_KCONTIG;  // row-info table needed
     static constexpr size_t ctile_bytes = (size_t)MT * (NT + 4) * sizeof(float);
     template <typename ST>
-    static constexpr size_t ops_bytes() { return (size_t)2 * (MT + NT) * LDK * sizeof(ST); }
+    static constexpr size_t ops_bytes() { return (size_t)2 * (a_elems<ST>() + b_elems<ST>()) * sizeof(ST); }
     static constexpr size_t rows_bytes = ROWS ? (size_t)2 * KC * sizeof(typename P::RowInfo) : 0;
     template <typename ST>
     static constexpr size_t lds_bytes() {
@@ -169,6 +180,12 @@ template <typename ST, int PER> struct Stage<ST, false, PER> {
     Vec8<ST> v[PER][8];
     float sc[PER][8];
     uint32_t ok[PER];  // bit i: row i of the 8 x 8 block is valid
+};
+
+// fp32 m-contiguous tile: 4 consecutive m of row k per unit.
+template <int PER> struct StageRows {
+    float4 v[PER];
+    bool ok[PER];
 };
 
 // Vectorised read of 8 floats of the C tile (row stride ldc, 16-byte aligned).
@@ -197,8 +214,10 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
     using S = GemmShape<P>;
     constexpr int MT = S::MT, NT = S::NT, KC = S::KC, LDK = S::LDK;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    ST* As = reinterpret_cast<ST*>(smem);   // [2][MT][LDK]
-    ST* Bs = As + 2 * MT * LDK;             // [2][NT][LDK]
+    constexpr bool AR = S::template a_rows<ST>(), BR = S::template b_rows<ST>();  // fp32 [k][m] tiles
+    constexpr int AE = S::template a_elems<ST>(), BE = S::template b_elems<ST>();
+    ST* As = reinterpret_cast<ST*>(smem);  // [2][MT][LDK] (or [2][KC][LDA_M])
+    ST* Bs = As + 2 * AE;                  // [2][NT][LDK] (or [2][KC][LDB_M])
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, c16 = lane & 15;
@@ -232,8 +251,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
         }
     }
 
-    Stage<ST, P::A_KCONTIG, S::A_PER> sa;
-    Stage<ST, P::B_KCONTIG, S::B_PER> sb;
+    std::conditional_t<AR, StageRows<S::A_PER4>, Stage<ST, P::A_KCONTIG, S::A_PER>> sa;
+    std::conditional_t<BR, StageRows<S::B_PER4>, Stage<ST, P::B_KCONTIG, S::B_PER>> sb;
     // row infos of chunks (m/n-contiguous operands), double-buffered in LDS
     typename P::RowInfo* rinfo =
         reinterpret_cast<typename P::RowInfo*>(smem + S::template ops_bytes<ST>());
@@ -268,6 +287,15 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
                 sa.ok[j] = p != nullptr;
                 sa.v[j] = vec8_load<ST>(p ? p : P::a_fallback(args));
             }
+        } else if constexpr (AR) {
+#pragma unroll
+            for (int j = 0; j < S::A_PER4; ++j) {
+                const int u = (tid + 256 * j) % S::A_U4, kr = u / (MT / 4), m4 = (u % (MT / 4)) * 4;
+                const typename P::RowInfo ri = rinfo[rbuf * KC + kr];
+                const int m8 = m0 + (m4 & ~7);
+                sa.ok[j] = P::a_kok(args, batch, ri, m8);
+                sa.v[j] = *reinterpret_cast<const float4*>(P::a_kaddr(args, batch, ri, m8) + (m4 & 7));
+            }
         } else {
 #pragma unroll
             for (int j = 0; j < S::A_PER; ++j) {
@@ -298,6 +326,15 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
                 sb.ok[j] = p != nullptr;
                 sb.v[j] = vec8_load<ST>(p ? p : P::b_fallback(args));
             }
+        } else if constexpr (BR) {
+#pragma unroll
+            for (int j = 0; j < S::B_PER4; ++j) {
+                const int u = (tid + 256 * j) % S::B_U4, kr = u / (NT / 4), n4 = (u % (NT / 4)) * 4;
+                const typename P::RowInfo ri = rinfo[rbuf * KC + kr];
+                const int n8 = n0 + (n4 & ~7);
+                sb.ok[j] = P::b_kok(args, batch, ri, n8);
+                sb.v[j] = *reinterpret_cast<const float4*>(P::b_kaddr(args, batch, ri, n8) + (n4 & 7));
+            }
         } else {
 #pragma unroll
             for (int j = 0; j < S::B_PER; ++j) {
@@ -324,8 +361,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
         // row-info load): wait for all of them here, explicitly, so that the
         // compiler's wait tracking does not carry them round the loop.
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        ST* a = As + buf * MT * LDK;
-        ST* b = Bs + buf * NT * LDK;
+        ST* a = As + buf * AE;
+        ST* b = Bs + buf * BE;
         if constexpr (P::A_KCONTIG) {
 #pragma unroll
             for (int j = 0; j < S::A_PER; ++j) {
@@ -335,6 +372,14 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
                     if (P::A_SCALED) x = vec8_scale<ST>(x, ascale[j]);
                     vec8_store<ST>(a + (v / (KC / 8)) * LDK + (v % (KC / 8)) * 8, x);
                 }
+            }
+        } else if constexpr (AR) {
+#pragma unroll
+            for (int j = 0; j < S::A_PER4; ++j) {
+                const int u = tid + 256 * j, kr = u / (MT / 4), m4 = (u % (MT / 4)) * 4;
+                if (u < S::A_U4)
+                    *reinterpret_cast<float4*>(a + kr * S::LDA_M + m4) =
+                        sa.ok[j] ? sa.v[j] : make_float4(0.f, 0.f, 0.f, 0.f);
             }
         } else {
 #pragma unroll
@@ -360,6 +405,14 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
                 const int v = tid + 256 * j;
                 if (v < S::B_VECS)
                     vec8_store<ST>(b + (v / (KC / 8)) * LDK + (v % (KC / 8)) * 8, sb.ok[j] ? sb.v[j] : vec8_zero<ST>());
+            }
+        } else if constexpr (BR) {
+#pragma unroll
+            for (int j = 0; j < S::B_PER4; ++j) {
+                const int u = tid + 256 * j, kr = u / (NT / 4), n4 = (u % (NT / 4)) * 4;
+                if (u < S::B_U4)
+                    *reinterpret_cast<float4*>(b + kr * S::LDB_M + n4) =
+                        sb.ok[j] ? sb.v[j] : make_float4(0.f, 0.f, 0.f, 0.f);
             }
         } else {
 #pragma unroll
@@ -403,22 +456,37 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
         commit(0);
         __syncthreads();
     } else {
-        // both operand buffers (A at As, B at Bs = As + 2 MT LDK), all in LDS
-        for (int e = tid; e < 2 * (MT + NT) * LDK / 8; e += 256) vec8_store<ST>(As + 8 * e, vec8_zero<ST>());
+        // both operand buffers (A at As, B right after them), all in LDS
+        for (int e = tid; e < 2 * (AE + BE) / 8; e += 256) vec8_store<ST>(As + 8 * e, vec8_zero<ST>());
         __syncthreads();
     }
     auto mfma_chunk = [&](int buf) {
-        const ST* a = As + buf * MT * LDK;
-        const ST* b = Bs + buf * NT * LDK;
+        const ST* a = As + buf * AE;
+        const ST* b = Bs + buf * BE;
+        // k = ks + 8 g + j of operand row `row` from a [k][m] tile
+        auto frag_rows = [&](const ST* t, int ld, int row, int ks) {
+            Frag8<ST> f;
+            if constexpr (sizeof(ST) == 4) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) f.v[j] = t[(ks + 8 * g + j) * ld + row];
+            }
+            return f;
+        };
 #pragma unroll
         for (int ks = 0; ks < KC; ks += 32) {
             Frag8<ST> fa[S::FM], fb[S::FN];
 #pragma unroll
-            for (int i = 0; i < S::FM; ++i)
-                fa[i] = frag8_load<ST>(a + (wm * S::WTM + i * 16 + c16) * LDK + ks + 8 * g);
+            for (int i = 0; i < S::FM; ++i) {
+                const int row = wm * S::WTM + i * 16 + c16;
+                if constexpr (AR) fa[i] = frag_rows(a, S::LDA_M, row, ks);
+                else fa[i] = frag8_load<ST>(a + row * LDK + ks + 8 * g);
+            }
 #pragma unroll
-            for (int j = 0; j < S::FN; ++j)
-                fb[j] = frag8_load<ST>(b + (wn * S::WTN + j * 16 + c16) * LDK + ks + 8 * g);
+            for (int j = 0; j < S::FN; ++j) {
+                const int row = wn * S::WTN + j * 16 + c16;
+                if constexpr (BR) fb[j] = frag_rows(b, S::LDB_M, row, ks);
+                else fb[j] = frag8_load<ST>(b + row * LDK + ks + 8 * g);
+            }
 #pragma unroll
             for (int i = 0; i < S::FM; ++i)
 #pragma unroll
@@ -459,6 +527,12 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
     if constexpr (kSplitK<P>) P::epilogue_split(args, batch, split, m0, n0, Cs, LDC, tid);
     else P::epilogue(args, batch, m0, n0, Cs, LDC, tid, smem + S::ctile_bytes);
 }
+
+// Workgroups from which a launch's tiles count as filling the chip (one per
+// CU); with fewer, fp32 launches take the policies' SMALL tiles.  fp32 MFMAs
+// run at 256 FLOP per clock and CU, so a 64 x 192 x 512 tile alone takes 25 us
+// at best: 32 such QKV tiles took 49 us, 192 of 32 x 64 take 15.7.
+constexpr int kFullChip = 256;
 
 template <typename ST, class P>
 int launch_gemm(const typename P::Args& args, int nblocks, hipStream_t stream) {

@@ -25,9 +25,9 @@ namespace mosa {
 
 namespace {
 
-template <typename ST, int DH>
+template <typename ST, int DH, bool SMALL = false>
 struct OutProjPolicy {
-    static constexpr int MT = 64, NT = 128, KC = sizeof(ST) == 2 ? DH : 32, WM = 2, WN = 2;
+    static constexpr int MT = SMALL ? 32 : 64, NT = SMALL ? 64 : 128, KC = sizeof(ST) == 2 ? DH : 32, WM = 2, WN = 2;
     static constexpr size_t EPI_LDS = 0;
     static constexpr bool A_KCONTIG = true, B_KCONTIG = false, A_SCALED = false;
     struct Args {
@@ -84,9 +84,9 @@ struct OutProjPolicy {
     }
 };
 
-template <typename ST, int DH>
+template <typename ST, int DH, bool SMALL = false>
 struct OutCombinePolicy {
-    static constexpr int MT = 64, NT = 128, KC = 32, WM = 2, WN = 2;
+    static constexpr int MT = SMALL ? 32 : 64, NT = SMALL ? 64 : 128, KC = 32, WM = 2, WN = 2;
     static constexpr size_t EPI_LDS = kCombineLds;
     static constexpr bool A_KCONTIG = true, B_KCONTIG = false, A_SCALED = false;
     struct Args {
@@ -143,9 +143,9 @@ struct OutCombinePolicy {
 
 // The dense heads' part alone ([B, T, d] in the storage type, here fp32) for
 // combine_rows_kernel to start from.
-template <typename ST, int DH>
-struct OutDensePolicy : OutCombinePolicy<ST, DH> {
-    using Base = OutCombinePolicy<ST, DH>;
+template <typename ST, int DH, bool SMALL>
+struct OutDensePolicy : OutCombinePolicy<ST, DH, SMALL> {
+    using Base = OutCombinePolicy<ST, DH, SMALL>;
     static constexpr size_t EPI_LDS = 0;
     struct Args : Base::Args {
         float* base;
@@ -250,7 +250,6 @@ struct OutProjRowPolicy {
 
 template <typename ST, int DH>
 int run_proj(const ST* A, const ST* Wo, int B, int d, int H, int k, ST* Xo, hipStream_t stream) {
-    using P = OutProjPolicy<ST, DH>;
     const int M = B * k;
     if constexpr (sizeof(ST) == 2) {
         const long long out_bytes = (long long)M * H * d * 2;
@@ -262,8 +261,15 @@ int run_proj(const ST* A, const ST* Wo, int B, int d, int H, int k, ST* Xo, hipS
             return launch_rowgemm<R>(ra, H * ntiles * splits, stream);
         }
     }
-    typename P::Args a{A, Wo, Xo, d, H, k, M, (M + P::MT - 1) / P::MT, (d + P::NT - 1) / P::NT};
-    return launch_gemm<ST, P>(a, H * a.mtiles * a.ntiles, stream);
+    auto go = [&](auto small) {
+        using P = OutProjPolicy<ST, DH, decltype(small)::value>;
+        typename P::Args a{A, Wo, Xo, d, H, k, M, (M + P::MT - 1) / P::MT, (d + P::NT - 1) / P::NT};
+        return launch_gemm<ST, P>(a, H * a.mtiles * a.ntiles, stream);
+    };
+    if constexpr (sizeof(ST) == 4) {
+        if ((M + 63) / 64 * ((d + 127) / 128) * H < kFullChip) return go(std::true_type{});
+    }
+    return go(std::false_type{});
 }
 
 template <typename ST, int DH>
@@ -283,11 +289,15 @@ int run_combine(const ST* Ad, const ST* Wod, const int16_t* slot, const ST* Xo, 
                 typename P2::Args a2{(const uint16_t*)Ad, (const uint16_t*)Wod, base, T, d, Hd, mt, nt};
                 e = launch_gemm2<P2>(a2, B * mt * nt, stream);
             } else {
-                using PD = OutDensePolicy<ST, DH>;
-                typename PD::Args ad{};
-                static_cast<typename P::Args&>(ad) = a;
-                ad.base = base;
-                e = launch_gemm<ST, PD>(ad, B * a.mtiles * a.ntiles, stream);
+                auto go = [&](auto small) {
+                    using PD = OutDensePolicy<ST, DH, decltype(small)::value>;
+                    const int mt = (T + PD::MT - 1) / PD::MT, nt = (d + PD::NT - 1) / PD::NT;
+                    typename PD::Args ad{};
+                    static_cast<typename PD::Base::Args&>(ad) = {Ad, Wod, slot, Xo, Y, T, d, H, k, Hd, accumulate, mt, nt};
+                    ad.base = base;
+                    return launch_gemm<ST, PD>(ad, B * mt * nt, stream);
+                };
+                e = B * a.mtiles * a.ntiles < kFullChip ? go(std::true_type{}) : go(std::false_type{});
             }
             if (e | mk("out_dense")) return -1;
         }

@@ -21,9 +21,11 @@ namespace mosa {
 
 namespace {
 
-template <typename ST, int DH>
+// fp32 storage.  SMALL: 32 rows and one of Q, K, V per workgroup.
+template <typename ST, int DH, bool SMALL>
 struct QkvPolicy {
-    static constexpr int MT = 64, NT = 3 * DH, KC = sizeof(ST) == 2 ? 64 : 32, WM = 2, WN = 2;
+    static constexpr int MT = SMALL ? 32 : 64, NT = SMALL ? DH : 3 * DH, KC = 32, WM = 2, WN = 2;
+    static constexpr int NTILES = 3 * DH / NT;
     static constexpr size_t EPI_LDS = 0;
     static constexpr bool A_KCONTIG = true, B_KCONTIG = false, A_SCALED = false;
     struct Args {
@@ -47,9 +49,10 @@ struct QkvPolicy {
     __device__ static const ST* b_fallback(const Args& a) { return a.W0; }
 
     __device__ static void tile(const Args& a, int logical, int& batch, int& m0, int& n0) {
-        batch = logical / a.mtiles;
-        m0 = (logical % a.mtiles) * MT;
-        n0 = 0;
+        const int per = a.mtiles * NTILES, rem = logical % per;
+        batch = logical / per;
+        m0 = (rem / NTILES) * MT;
+        n0 = (rem % NTILES) * NT;
     }
     __device__ static int k_size(const Args& a, int) { return a.d; }
     __device__ static ARef a_row(const Args& a, int h, int m, float&) {
@@ -71,7 +74,8 @@ struct QkvPolicy {
         return W + ((size_t)h * a.d + max(r.k, 0)) * DH + (n8 % DH);
     }
     __device__ static bool b_kok(const Args&, int, const RowInfo& r, int) { return r.k >= 0; }
-    __device__ static void epilogue(const Args& a, int h, int m0, int, const float* Cs, int ldc, int tid, unsigned char*) {
+    __device__ static void epilogue(const Args& a, int h, int m0, int n0, const float* Cs, int ldc, int tid,
+                                    unsigned char*) {
         constexpr int VPR = NT / 8;  // vectors per row
         for (int v = tid; v < MT * VPR; v += 256) {
             const int ml = v / VPR, c = (v % VPR) * 8;
@@ -80,8 +84,8 @@ struct QkvPolicy {
             const int b = m / a.n, i = m % a.n;
             float x[8];
             cs_load8(Cs, ldc, ml, c, x);
-            rope_cols(a, h, b, i, c, x);
-            vec8_store<ST>(a.out + (((size_t)b * a.H + h) * a.n + i) * NT + c, vec8_from_f32<ST>(x));
+            rope_cols(a, h, b, i, n0 + c, x);
+            vec8_store<ST>(a.out + (((size_t)b * a.H + h) * a.n + i) * (3 * DH) + n0 + c, vec8_from_f32<ST>(x));
         }
     }
     // columns c .. c + 7 of row (b, h, i): the rotary encoding of q and k
@@ -285,9 +289,12 @@ int run(const ST* X, const int32_t* I, const ST* Wq, const ST* Wk, const ST* Wv,
         };
         return narrow || (I && narrow_rows(B * n, H)) ? go(std::integral_constant<int, 64>{}) : go(std::integral_constant<int, 128>{});
     } else {
-        using P = QkvPolicy<ST, DH>;
-        typename P::Args a{X, I, Wq, Wk, Wv, out, T, d, H, n, B * n, (B * n + P::MT - 1) / P::MT, rope};
-        return launch_gemm<ST, P>(a, a.mtiles * H, stream);
+        auto go = [&](auto small) {
+            using P = QkvPolicy<ST, DH, decltype(small)::value>;
+            typename P::Args a{X, I, Wq, Wk, Wv, out, T, d, H, n, B * n, (B * n + P::MT - 1) / P::MT, rope};
+            return launch_gemm<ST, P>(a, a.mtiles * H * P::NTILES, stream);
+        };
+        return (B * n + 63) / 64 * H < kFullChip ? go(std::true_type{}) : go(std::false_type{});
     }
 }
 

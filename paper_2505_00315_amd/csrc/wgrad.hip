@@ -27,9 +27,12 @@ namespace mosa {
 
 namespace {
 
-template <typename ST, int DH, bool ROUTER, bool GATHER>
+// SMALL (fp32): one of dW^Q, dW^K, dW^V (or the router column) per workgroup.
+template <typename ST, int DH, bool ROUTER, bool GATHER, bool SMALL = false>
 struct WgradQkvPolicy {
-    static constexpr int MT = 64, NT = 3 * DH + (ROUTER ? 16 : 0), KC = sizeof(ST) == 2 ? 64 : 32, WM = 4, WN = 1;
+    static constexpr int NALL = 3 * DH + (ROUTER ? 16 : 0);  // columns of a partial row
+    static constexpr int MT = 64, NT = SMALL ? DH : NALL, KC = sizeof(ST) == 2 ? 64 : 32, WM = SMALL ? 2 : 4, WN = 4 / WM;
+    static constexpr int NTILES = (NALL + NT - 1) / NT;
     static constexpr size_t EPI_LDS = 0;
     static constexpr bool A_KCONTIG = false, B_KCONTIG = false, A_SCALED = false, SPLITK = true;
     struct Args {
@@ -58,12 +61,12 @@ struct WgradQkvPolicy {
     __device__ static const ST* a_fallback(const Args& a) { return a.X; }
     __device__ static const ST* b_fallback(const Args& a) { return a.dQKV; }
     __device__ static void tile_split(const Args& a, int logical, int& h, int& m0, int& n0, int& split) {
-        const int per = a.H * a.mtiles;
+        const int per = a.H * a.mtiles * NTILES;
         split = logical / per;
-        const int rem = logical % per;
-        h = rem / a.mtiles;
-        m0 = (rem % a.mtiles) * MT;
-        n0 = 0;
+        const int rem = logical % per, mn = rem % (a.mtiles * NTILES);
+        h = rem / (a.mtiles * NTILES);
+        m0 = (mn / NTILES) * MT;
+        n0 = (mn % NTILES) * NT;
     }
     __device__ static void k_range(const Args& a, int split, int K, int& kbeg, int& kend) {
         kbeg = split * a.cps * KC;
@@ -88,21 +91,24 @@ struct WgradQkvPolicy {
     __device__ static float a_kscale(const Args&, int, const RowInfo&) { return 1.f; }
     // B[r][n] = dQ | dK | dV | (dz, 0...) of row r
     __device__ static const ST* b_kaddr(const Args& a, int, const RowInfo& r, int n8) {
-        return n8 < 3 * DH ? a.dQKV + (size_t)r.ri * (3 * DH) + n8 : a.dz16 + (size_t)r.ri * 16 + (n8 - 3 * DH);
+        return n8 < 3 * DH ? a.dQKV + (size_t)r.ri * (3 * DH) + n8
+                           : a.dz16 + (size_t)r.ri * 16 + min(n8 - 3 * DH, 8);
     }
-    __device__ static bool b_kok(const Args&, int, const RowInfo& r, int) { return r.b >= 0; }
-    __device__ static void epilogue(const Args& a, int h, int m0, int, const float* Cs, int ldc, int tid, unsigned char*) {
-        constexpr int VPR = 3 * DH / 8;
+    __device__ static bool b_kok(const Args&, int, const RowInfo& r, int n8) { return r.b >= 0 && n8 < NALL; }
+    __device__ static void epilogue(const Args& a, int h, int m0, int n0, const float* Cs, int ldc, int tid,
+                                    unsigned char*) {
+        constexpr int VPR = NT / 8;
         for (int v = tid; v < MT * VPR; v += 256) {
-            const int ml = v / VPR, nn = (v % VPR) * 8;
+            const int ml = v / VPR, nl = (v % VPR) * 8, nn = n0 + nl;
             const int c = m0 + ml;
-            if (c >= a.d) continue;
+            if (c >= a.d || nn >= 3 * DH) continue;
             float x[8];
-            cs_load8(Cs, ldc, ml, nn, x);
+            cs_load8(Cs, ldc, ml, nl, x);
             ST* W = nn < DH ? a.dWq : (nn < 2 * DH ? a.dWk : a.dWv);
             vec8_store<ST>(W + ((size_t)h * a.d + c) * DH + (nn % DH), vec8_from_f32<ST>(x));
         }
-        if (ROUTER && tid < MT && m0 + tid < a.d) st1<ST>(a.dWr + (size_t)h * a.d + m0 + tid, Cs[tid * ldc + 3 * DH]);
+        if (ROUTER && n0 + NT > 3 * DH && tid < MT && m0 + tid < a.d)
+            st1<ST>(a.dWr + (size_t)h * a.d + m0 + tid, Cs[tid * ldc + 3 * DH - n0]);
     }
     __device__ static void epilogue_split(const Args& a, int h, int split, int m0, int n0, const float* Cs, int ldc,
                                           int tid) {
@@ -112,11 +118,11 @@ struct WgradQkvPolicy {
         }
         constexpr int VPR = NT / 4;  // float4 per row
         for (int v = tid; v < MT * VPR; v += 256) {
-            const int ml = v / VPR, nn = (v % VPR) * 4;
+            const int ml = v / VPR, nl = (v % VPR) * 4, nn = n0 + nl;
             const int c = m0 + ml;
-            if (c >= a.d) continue;
-            const float4 x = *reinterpret_cast<const float4*>(Cs + ml * ldc + nn);
-            *reinterpret_cast<float4*>(a.part + (((size_t)split * a.H + h) * a.d + c) * NT + nn) = x;
+            if (c >= a.d || nn >= NALL) continue;
+            const float4 x = *reinterpret_cast<const float4*>(Cs + ml * ldc + nl);
+            *reinterpret_cast<float4*>(a.part + (((size_t)split * a.H + h) * a.d + c) * NALL + nn) = x;
         }
     }
 };
@@ -146,9 +152,9 @@ __global__ __launch_bounds__(256) void wgrad_qkv_reduce_kernel(const float* __re
     }
 }
 
-template <typename ST, int DH, bool GATHER>
+template <typename ST, int DH, bool GATHER, bool SMALL = false>
 struct WgradOPolicy {
-    static constexpr int MT = DH, NT = 128, KC = sizeof(ST) == 2 ? 64 : 32, WM = 2, WN = 2;
+    static constexpr int MT = DH, NT = SMALL ? 64 : 128, KC = sizeof(ST) == 2 ? 64 : 32, WM = 2, WN = 2;
     static constexpr size_t EPI_LDS = 0;
     static constexpr bool A_KCONTIG = false, B_KCONTIG = false, A_SCALED = false, SPLITK = true;
     struct Args {
@@ -448,6 +454,39 @@ int choose_splits(int base_tiles, int nchunks, int& cps) {
     return nchunks > 0 ? (nchunks + cps - 1) / cps : 1;
 }
 
+// Splits of a launch of `tiles` output tiles over `rows` rows; small: whether
+// the smaller tiles are taken (fp32, when the larger ones with their splits
+// leave CUs idle).
+struct WgradPlan {
+    int S, cps;
+    bool small;
+};
+template <class P, class PS>
+WgradPlan wgrad_plan(int tiles, int small_tiles, int rows, bool allow_small) {
+    WgradPlan w{1, 0, false};
+    const int nchunks = (rows + P::KC - 1) / P::KC;
+    w.S = choose_splits(tiles, nchunks, w.cps);
+    if (allow_small && w.S * tiles < kFullChip) {
+        w.small = true;
+        static_assert(P::KC == PS::KC, "same chunks");
+        w.S = choose_splits(small_tiles, nchunks, w.cps);
+    }
+    return w;
+}
+template <typename ST, int DH, bool ROUTER, bool GATHER>
+WgradPlan plan_qkv(int d, int H, int R) {
+    using P = WgradQkvPolicy<ST, DH, ROUTER, GATHER>;
+    using PS = WgradQkvPolicy<ST, DH, ROUTER, GATHER, true>;
+    const int mt = (d + P::MT - 1) / P::MT;
+    return wgrad_plan<P, PS>(H * mt, H * mt * PS::NTILES, R, sizeof(ST) == 4);
+}
+template <typename ST, int DH, bool GATHER>
+WgradPlan plan_o(int d, int H, int R) {
+    using P = WgradOPolicy<ST, DH, GATHER>;
+    using PS = WgradOPolicy<ST, DH, GATHER, true>;
+    return wgrad_plan<P, PS>(H * ((d + P::NT - 1) / P::NT), H * ((d + PS::NT - 1) / PS::NT), R, sizeof(ST) == 4);
+}
+
 // Stage names of the weight-gradient kernels (MoSA heads / dense heads).
 inline const char* wname(bool dense, int which, bool reduce) {
     static const char* const names[2][2][2] = {
@@ -488,10 +527,16 @@ int run_qkv_t(const ST* X, const int32_t* I, const ST* dQKV, const ST* dz16, int
             return e;
         }
     }
-    int cps;
-    const int S = choose_splits(H * mtiles, (R + P::KC - 1) / P::KC, cps);
-    typename P::Args a{X, I, dQKV, dz16, dWq, dWk, dWv, dWr, part, T, d, H, n, R, mtiles, S, cps, make_fastdiv(n)};
-    int e = launch_gemm<ST, P>(a, S * H * mtiles, stream);
+    const WgradPlan w = plan_qkv<ST, DH, ROUTER, GATHER>(d, H, R);
+    const int S = w.S;
+    auto go = [&](auto p) {
+        using PT = decltype(p);
+        typename PT::Args a{X, I, dQKV, dz16, dWq, dWk, dWv, dWr, part, T, d, H, n, R, mtiles, S, w.cps, make_fastdiv(n)};
+        return launch_gemm<ST, PT>(a, S * H * mtiles * PT::NTILES, stream);
+    };
+    int e;
+    if constexpr (sizeof(ST) == 4) e = w.small ? go(WgradQkvPolicy<ST, DH, ROUTER, GATHER, true>{}) : go(P{});
+    else e = go(P{});
     e |= mk(wname(dense, 0, false));
     if (S > 1 && e == 0) {
         const int total = H * d * (3 * DH / 8 + (ROUTER ? 1 : 0));
@@ -516,7 +561,7 @@ int run_o_t(const ST* dY, const int32_t* I, const ST* A, int B, int T, int d, in
             const Marker& mk, hipStream_t stream) {
     using P = WgradOPolicy<ST, DH, GATHER>;
     const bool dense = !GATHER;
-    const int ntiles = (d + P::NT - 1) / P::NT, R = B * n;
+    const int R = B * n;
     if constexpr (sizeof(ST) == 2 && GATHER) {
         using P2 = WgradOPolicy2<DH>;
         if (const int rows = wgrad2_table_rows<P2>(R, d)) {
@@ -542,10 +587,17 @@ int run_o_t(const ST* dY, const int32_t* I, const ST* A, int B, int T, int d, in
             return e;
         }
     }
-    int cps;
-    const int S = choose_splits(H * ntiles, (R + P::KC - 1) / P::KC, cps);
-    typename P::Args a{dY, I, A, dWo, part, T, d, H, n, R, ntiles, S, cps, make_fastdiv(n)};
-    int e = launch_gemm<ST, P>(a, S * H * ntiles, stream);
+    const WgradPlan w = plan_o<ST, DH, GATHER>(d, H, R);
+    const int S = w.S;
+    auto go = [&](auto p) {
+        using PT = decltype(p);
+        const int nt = (d + PT::NT - 1) / PT::NT;
+        typename PT::Args a{dY, I, A, dWo, part, T, d, H, n, R, nt, S, w.cps, make_fastdiv(n)};
+        return launch_gemm<ST, PT>(a, S * H * nt, stream);
+    };
+    int e;
+    if constexpr (sizeof(ST) == 4) e = w.small ? go(WgradOPolicy<ST, DH, GATHER, true>{}) : go(P{});
+    else e = go(P{});
     e |= mk(wname(dense, 1, false));
     if (S > 1 && e == 0) {
         const size_t n8 = (size_t)H * DH * d / 8;
@@ -607,17 +659,14 @@ int run_bwd_proj(const uint16_t* X, const uint16_t* dY, const int32_t* I, const 
 // Bytes of fp32 partial sums the two launches of one head group need.
 template <typename ST, int DH>
 size_t partial_bytes(int B, int d, int H, int n, bool router) {
-    using PQ = WgradQkvPolicy<ST, DH, true, true>;
-    using PO = WgradOPolicy<ST, DH, true>;
     const int R = B * n;
     if constexpr (sizeof(ST) == 2) {  // MoSA heads on the gathered-row engine: no partials
         if (router && wgrad2_table_rows<WgradQkvPolicy2<DH>>(R, d) && wgrad2_table_rows<WgradOPolicy2<DH>>(R, d))
             return 0;
     }
-    int cps;
-    const int mtiles = (d + PQ::MT - 1) / PQ::MT, ntiles = (d + PO::NT - 1) / PO::NT;
-    const int sq = choose_splits(H * mtiles, (R + PQ::KC - 1) / PQ::KC, cps);
-    const int so = choose_splits(H * ntiles, (R + PO::KC - 1) / PO::KC, cps);
+    // (the plans do not depend on GATHER)
+    const int sq = router ? plan_qkv<ST, DH, true, true>(d, H, R).S : plan_qkv<ST, DH, false, false>(d, H, R).S;
+    const int so = plan_o<ST, DH, true>(d, H, R).S;
     const size_t nq = 3 * DH + (router ? 16 : 0);
     size_t bq = sq > 1 ? (size_t)sq * H * d * nq * 4 : 0;
     size_t bo = so > 1 ? (size_t)so * H * DH * d * 4 : 0;

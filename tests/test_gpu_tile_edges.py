@@ -37,3 +37,19 @@ def test_row_tiles(orc, batch, k, rope, causal):
     if k % 16 == 0:
         _check(orc, wl.small(batch=batch, seq_len=131, d_model=64, d_head=64, heads=2, k=k, rope=rope, causal=causal,
                              seed=100 * batch + k + 1))
+
+
+# fp32: the small tiles (few workgroups) and the large ones (64 heads of 260
+# rows), rows and blocks of 16 short of, at and past their edges, 1 to 8 waves
+# sharing a block's loop, dense heads with and without a window
+@pytest.mark.parametrize("kw", [
+    dict(seq_len=15, k=7, heads=1, dense_heads=1, d_head=64),
+    dict(seq_len=33, k=17, heads=2, dense_heads=1, d_model=128, d_head=32, rope=True),
+    dict(seq_len=65, k=33, heads=2, dense_heads=2, d_model=192, d_head=64, window=16),
+    dict(seq_len=129, k=65, heads=3, dense_heads=1, d_head=64, causal=False),
+    dict(seq_len=150, k=130, heads=64, dense_heads=0, d_head=32, batch=2),
+    dict(seq_len=150, k=130, heads=64, dense_heads=0, d_head=64, batch=2, rope=True),
+    dict(seq_len=300, k=3, heads=1, dense_heads=9, d_model=256, d_head=64, window=100),
+])
+def test_f32_tiles(orc, kw):
+    _check(orc, wl.small(dtype="f32", seed=77, **kw))
