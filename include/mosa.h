@@ -19,8 +19,8 @@
  *     per device: kernels that need more than 64 KB of LDS have that limit set
  *     on the current device before each launch; mosa_forward_noalloc keeps
  *     the address of its static scratch; and the untimed forward and backward
- *     of a layer with both MoSA and dense heads run the dense heads' kernels
- *     on an auxiliary stream of the device (non-blocking, default priority,
+ *     of a layer with both MoSA and dense heads run the dense heads' kernels,
+ *     where there is enough work in them, on an auxiliary stream of the device (non-blocking, default priority,
  *     created at the first such call and kept until the process ends), forked
  *     from and joined back into `stream` with events inside the call, so the
  *     two sets of heads share the CUs.  The enqueue of such calls is

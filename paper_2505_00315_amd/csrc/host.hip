@@ -206,6 +206,29 @@ int aux_join(AuxStream* ax, hipStream_t main) {
     return hipEventRecord(ax->join, ax->s) != hipSuccess || hipStreamWaitEvent(main, ax->join, 0) != hipSuccess;
 }
 
+// Whether an untimed call with both kinds of heads runs them on two streams.
+// A fork and a join cost about 25 us of host time (an event recorded on one
+// stream and waited for on another about 13, a kernel launch 2.7): a layer whose
+// kernels take less than the host then runs slower on two streams than on
+// one, a larger one gains up to the shorter of its two chains.  So the line is
+// drawn by the work of both chains.  Measured with 4 dense and 12 MoSA heads,
+// d 1024, k = T / 32, bf16, one stream against two (us per pass; the latter on
+// a faster and a slower host): forward, 333 tokens 63 against 67-89, 2048 69 /
+// 67-90, 4096 72 / 68-86, 8192 86 / 82-84; forward and backward 136 / 161-196,
+// 166 / 167-210, 184 / 167-207, 244 / 226.  The line, 6 GFLOP of forward, lies
+// between 2048 and 4096 of those tokens; the MoSA heads' products count twice
+// (they run at about half the dense heads' rate).  fp32 chains are several
+// times longer at the same size and gain from 128 tokens on (108 against 84-89).
+bool two_streams(const mosa_shape* s) {
+    if (s->heads == 0 || s->dense_heads == 0 || !combine_split_ok(s->d_model, s->heads)) return false;
+    if (s->dtype == MOSA_F32) return true;
+    const double B = s->batch, T = s->seq_len, d = s->d_model, dh = s->d_head, k = s->k;
+    const double keys = s->window > 0 && s->window < s->seq_len ? s->window : s->causal ? T / 2 : T;
+    const double dense = B * s->dense_heads * T * dh * (8 * d + 4 * keys);
+    const double mosa = B * s->heads * (k * dh * (8 * d + 4 * k) + 2 * T * d);
+    return dense + 2 * mosa >= 6e9;
+}
+
 }  // namespace
 
 extern "C" {
@@ -284,10 +307,10 @@ int forward_impl(const mosa_shape* s, const void* X, const mosa_weights* w, void
         e |= launch_rope_table(T, dh, s->rope_base, rope, stream);
         e |= sm.mark("rope_table");
     }
-    // the dense heads on the auxiliary stream (untimed calls with both kinds of heads)
+    // the dense heads on the auxiliary stream (untimed calls, see two_streams)
     std::unique_lock<std::mutex> lock(g_aux_mu, std::defer_lock);
     AuxStream* ax = nullptr;
-    if (!ev && H > 0 && Hd > 0 && combine_split_ok(d, H)) {
+    if (!ev && two_streams(s)) {
         lock.lock();
         ax = aux_stream();
         if (ax && aux_fork(ax, stream)) return MOSA_ERR_HIP;
@@ -418,10 +441,10 @@ int mosa_backward_timed(const mosa_shape* s, const void* X, const mosa_weights* 
     void* dWr = g->dWr ? g->dWr : at<char>(scratch, L.dwr);
 
     const Marker mk = sm.marker();
-    // the dense heads on the auxiliary stream (untimed calls with both kinds of heads)
+    // the dense heads on the auxiliary stream (untimed calls, see two_streams)
     std::unique_lock<std::mutex> lock(g_aux_mu, std::defer_lock);
     AuxStream* ax = nullptr;
-    if (!ev && H > 0 && Hd > 0 && combine_split_ok(d, H)) {
+    if (!ev && two_streams(s)) {
         lock.lock();
         ax = aux_stream();
         if (ax && aux_fork(ax, stream)) return MOSA_ERR_HIP;
