@@ -34,6 +34,9 @@ namespace {
 
 constexpr int kBhDH = 64, kBhJ = 3 * kBhDH, kBhStages = 3;
 
+// Zeros for the rows past the end of a head's rows.
+static __device__ __attribute__((aligned(16))) const uint16_t bh_zero[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+
 struct BhArgs {
     const uint16_t* X;      // [B, T, d]
     const uint16_t* dY;     // [B, T, d]
@@ -127,7 +130,7 @@ struct RowTileLoader {
                 src[jj] = base + ((size_t)b * a.T + a.I[ri]) * a.d + 8 * (su ^ tr_swz(r));
                 step[jj] = 1;
             } else {
-                src[jj] = g2_zero;
+                src[jj] = bh_zero;
                 step[jj] = 0;
             }
         }
@@ -158,7 +161,7 @@ __device__ void bh_job_w1(const BhArgs& a, int h, int t0, int t1, unsigned char*
             const int p = 64 * (wave + 4 * jj) + lane, rl = p >> 5, su = p & 31, r = 128 * half + rl;
             const int gu = (su & ~7) | ((su & 7) ^ tr_swz(r));
             const int ri = bh_row(a, h, r);
-            const uint16_t* src = g2_zero;
+            const uint16_t* src = bh_zero;
             if (ri >= 0 && gu < 24) src = a.dQKV + (size_t)ri * kBhJ + 8 * gu;
             else if (ri >= 0 && gu < 26) src = a.dz16 + (size_t)ri * 16 + 8 * (gu - 24);
             lds_load16(src, lbase + 1024 * wave_s + 4096 * jj);
@@ -270,7 +273,7 @@ __device__ void bh_job_w2(const BhArgs& a, int h, int t0, int t1, unsigned char*
     for (int jj = 0; jj < NR; ++jj) {
         const int p = 64 * (wave + 4 * jj) + lane, r = p >> 3, su = p & 7;
         const int ri = bh_row(a, h, r);
-        const uint16_t* src = ri >= 0 ? a.A + (size_t)ri * kBhDH + 8 * (su ^ tr_swz(r)) : g2_zero;
+        const uint16_t* src = ri >= 0 ? a.A + (size_t)ri * kBhDH + 8 * (su ^ tr_swz(r)) : bh_zero;
         lds_load16(src, lbase + 1024 * wave_s + 4096 * jj);
     }
     wait_vmcnt<0>();

@@ -34,12 +34,26 @@
 //
 // Optional (all off by default):
 //   KGATHER: the rows along k are gathered (both operands m-contiguous).  The
-//     workgroup first fills an LDS table with k_row(args, batch, k, K) -> int2
-//     for every k of its range (K need not be a multiple of KC; the table
-//     covers the padded range), and a lane's address for row k is
-//     base + tab[k].{x|y} * stride with base and stride from
-//     a_mlane(args, batch, m8, base, stride) (A_TAB picks x or y; likewise
-//     b_mlane / B_TAB).  A negative table entry reads zeros.
+//     workgroup first fills an LDS table with k_row(args, batch, k) -> uint2 for
+//     every k of its range (clamped to the last one in the padded part), and a
+//     lane's address for row k is a_mlane(args, batch, m8) + 16 tab[k].x bytes
+//     (.y with A_TAB 1; likewise b_mlane / B_TAB): one 64-bit shift and add per
+//     load, as the loop has little room for address arithmetic beside the
+//     MFMAs.  K need not be a multiple of KC: the rows past K of the last chunk
+//     are cleared in LDS.
+//   MULTI (with KGATHER and EPI_REGS): a workgroup runs tiles(args, logical)
+//     output tiles one after the other, adjacent along M (MULTI_A, the A
+//     operand's columns move by MT per tile) or along N (the B operand's by
+//     NT), as one pipeline over all their chunks: the row table and the
+//     pipeline's fill are paid once, and the next tile's loads are in flight
+//     while a tile is stored.  STORES: the number of memory instructions that
+//     every wave issues at least while storing a tile (they count in the waits
+//     that follow; vector memory operations complete in issue order).
+//   ROW (with MULTI): a product of one fp32 weight per k with every column of
+//     the B tile beside the MFMAs, out[n] = sum_k f[k] B[k][n], by VALU from
+//     the B fragments in registers (the WM waves of a column block share its
+//     columns).  Another LDS table holds f = k_f(args, batch, k, K) (0 past K);
+//     store_row(args, batch, n, sum) writes a column's sum.
 //   A_INTERLEAVE: an m-contiguous A operand whose 16-row MFMA blocks are taken
 //     in pairs with interleaved columns (block 2p row i is M index
 //     32 p + 8 (i / 4) + i % 4, block 2p + 1 row i is 32 p + 8 (i / 4) + 4 + i % 4),
@@ -143,6 +157,12 @@ __device__ __forceinline__ int mswz(int k, int u) {
 
 template <class P, class = void> struct G2Gather : std::false_type {};
 template <class P> struct G2Gather<P, std::void_t<decltype(P::KGATHER)>> : std::bool_constant<P::KGATHER> {};
+template <class P, class = void> struct G2Multi : std::false_type {};
+template <class P> struct G2Multi<P, std::void_t<decltype(P::MULTI)>> : std::bool_constant<P::MULTI> {};
+template <class P, class = void> struct G2Row : std::false_type {};
+template <class P> struct G2Row<P, std::void_t<decltype(P::ROW)>> : std::bool_constant<P::ROW> {};
+template <class P, class = void> struct G2MultiA : std::false_type {};
+template <class P> struct G2MultiA<P, std::void_t<decltype(P::MULTI_A)>> : std::bool_constant<P::MULTI_A> {};
 template <class P, class = void> struct G2Interleave : std::false_type {};
 template <class P>
 struct G2Interleave<P, std::void_t<decltype(P::A_INTERLEAVE)>> : std::bool_constant<P::A_INTERLEAVE> {};
@@ -173,9 +193,6 @@ template <class P, class = void> struct G2BKoff : std::false_type {};
 template <class P>
 struct G2BKoff<P, std::void_t<decltype(P::b_koff(std::declval<const typename P::Args&>(), 0, 0))>> : std::true_type {};
 
-// Zeros for the rows past the end of a gathered range.
-static __device__ __attribute__((aligned(16))) const uint16_t g2_zero[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-
 template <class P>
 struct Gemm2Shape {
     static constexpr int MT = P::MT, NT = P::NT, KC = P::KC, WM = P::WM, WN = P::WN, STAGES = P::STAGES;
@@ -191,14 +208,17 @@ struct Gemm2Shape {
     static_assert(STAGES >= 2 && (STAGES - 1) * (IA + IB) <= 63, "vmcnt range");
     static constexpr bool KG = G2Gather<P>::value, IL = G2Interleave<P>::value, ER = G2EpiRegs<P>::value;
     static constexpr bool CA = G2ChunkAdd<P>::value;
+    static constexpr bool MU = G2Multi<P>::value, ROW = G2Row<P>::value;
+    static_assert(!ROW || (MU && WM <= 2 && FN % WM == 0), "row weights");
+    static_assert(!MU || (KG && ER), "several tiles need gathered k and the register epilogue");
     static_assert(!KG || (!P::A_KCONTIG && !P::B_KCONTIG), "gathered k needs m-contiguous operands");
     static_assert(!IL || (!P::A_KCONTIG && FM % 2 == 0), "interleaved A needs m-contiguous pairs of blocks");
     static_assert(!ER || IL, "register epilogue needs interleaved A");
     static constexpr size_t ctile_bytes = ER ? 0 : (size_t)MT * (NT + 4) * sizeof(float);
-    // LDS bytes; the k-row table of a gathered range (8 bytes per row of the
+    // LDS bytes; the k-row table of a gathered range (8 bytes per row, with row weights 12, of the
     // padded range) follows the stage buffers.
     static constexpr size_t lds_bytes(int ktab_rows = 0) {
-        const size_t ops = (size_t)STAGES * STAGE_BYTES + (KG ? (size_t)ktab_rows * 8 : 0);
+        const size_t ops = (size_t)STAGES * STAGE_BYTES + (KG ? (size_t)ktab_rows * (ROW ? 12 : 8) : 0);
         const size_t epi = ctile_bytes + P::EPI_LDS;
         return ops > epi ? ops : epi;
     }
@@ -236,9 +256,16 @@ __device__ __forceinline__ void gemm2_body(const typename P::Args& args, int log
     P::tile(args, logical, batch, m0, n0);
     const int K = P::k_size(args, batch);
     const int nchunks = S::KG ? (K + KC - 1) / KC : K / KC;
-    int2* ktab = reinterpret_cast<int2*>(smem + STG * S::STAGE_BYTES);
+    // gathered: row offsets of the two operands, and the row weights
+    uint32_t* ktab = reinterpret_cast<uint32_t*>(smem + STG * S::STAGE_BYTES);
+    float* kf = reinterpret_cast<float*>(ktab + 2 * nchunks * KC);
     if constexpr (S::KG) {
-        for (int i = tid; i < nchunks * KC; i += 256) ktab[i] = P::k_row(args, batch, i, K);
+        for (int i = tid; i < nchunks * KC; i += 256) {
+            const uint2 e = P::k_row(args, batch, min(i, K - 1));
+            ktab[i] = e.x;
+            ktab[nchunks * KC + i] = e.y;
+            if constexpr (S::ROW) kf[i] = P::k_f(args, batch, i, K);
+        }
         __syncthreads();
     }
 
@@ -247,8 +274,7 @@ __device__ __forceinline__ void gemm2_body(const typename P::Args& args, int log
     // so that the loop does plain pointer arithmetic.
     const ST* asrc[S::IA > 0 ? S::IA : 1];
     const ST* bsrc[S::IB > 0 ? S::IB : 1];
-    uint32_t astr[S::IA > 0 ? S::IA : 1], bstr[S::IB > 0 ? S::IB : 1];  // gathered: element stride per table unit
-    int akr[S::IA > 0 ? S::IA : 1], bkr[S::IB > 0 ? S::IB : 1];         // gathered: k row within the chunk
+    int akr[S::IA > 0 ? S::IA : 1], bkr[S::IB > 0 ? S::IB : 1];  // gathered: table index within the first chunk
 #pragma unroll
     for (int j = 0; j < S::IA; ++j) {
         const int p = 64 * (wave + 4 * j) + lane;  // unit of the tile
@@ -259,8 +285,8 @@ __device__ __forceinline__ void gemm2_body(const typename P::Args& args, int log
             constexpr int U = MT / 8;
             const int kr = p / U, pos = p % U;
             if constexpr (S::KG) {
-                P::a_mlane(args, batch, m0 + 8 * mswz<U>(kr, pos), asrc[j], astr[j]);
-                akr[j] = kr;
+                asrc[j] = P::a_mlane(args, batch, m0 + 8 * mswz<U>(kr, pos));
+                akr[j] = kr + (P::A_TAB ? nchunks * KC : 0);
             } else {
                 asrc[j] = P::a_maddr(args, batch, kr, m0 + 8 * mswz<U>(kr, pos));
             }
@@ -276,8 +302,8 @@ __device__ __forceinline__ void gemm2_body(const typename P::Args& args, int log
             constexpr int U = NT / 8;
             const int kr = p / U, pos = p % U;
             if constexpr (S::KG) {
-                P::b_mlane(args, batch, n0 + 8 * mswz<U>(kr, pos), bsrc[j], bstr[j]);
-                bkr[j] = kr;
+                bsrc[j] = P::b_mlane(args, batch, n0 + 8 * mswz<U>(kr, pos));
+                bkr[j] = kr + (P::B_TAB ? nchunks * KC : 0);
             } else {
                 bsrc[j] = P::b_maddr(args, batch, kr, n0 + 8 * mswz<U>(kr, pos));
             }
@@ -292,27 +318,24 @@ __device__ __forceinline__ void gemm2_body(const typename P::Args& args, int log
 
     // Gathered k: this lane's table entries for the next chunk to issue, read
     // one iteration ahead so that the LDS latency stays off the issue path.
-    int arv[S::IA > 0 ? S::IA : 1], brv[S::IB > 0 ? S::IB : 1];
+    uint32_t arv[S::IA > 0 ? S::IA : 1], brv[S::IB > 0 ? S::IB : 1];
     auto load_rows = [&](int c) {
         if constexpr (S::KG) {
-            const int cc = min(c, nchunks - 1);
+            const int cc = min(c, nchunks - 1) * KC;
 #pragma unroll
-            for (int j = 0; j < S::IA; ++j) {
-                const int2 e = ktab[cc * KC + akr[j]];
-                arv[j] = P::A_TAB ? e.y : e.x;
-            }
+            for (int j = 0; j < S::IA; ++j) arv[j] = ktab[cc + akr[j]];
 #pragma unroll
-            for (int j = 0; j < S::IB; ++j) {
-                const int2 e = ktab[cc * KC + bkr[j]];
-                brv[j] = P::B_TAB ? e.y : e.x;
-            }
+            for (int j = 0; j < S::IB; ++j) brv[j] = ktab[cc + bkr[j]];
         }
     };
-    // base + rv * stride, or the zero row for rv < 0 (branch-free)
-    auto gathered = [](const ST* base, uint32_t stride, int rv) {
-        const ST* p = base + (size_t)(uint32_t)max(rv, 0) * stride;
-        return rv >= 0 ? p : g2_zero;
+    // 16 bytes of a gathered row
+    auto gathered = [](const ST* base, uint32_t off16) {
+        return reinterpret_cast<const unsigned char*>(base) + ((size_t)off16 << 4);
     };
+    // Several tiles: chunks of all of them (`total`); the chunk within its tile
+    // and the operand column offset of the next chunk to be issued.
+    int total = nchunks, ichunk = 0, ishift = 0;
+    if constexpr (S::MU) total = nchunks * P::tiles(args, logical);
 
     // Issue the loads of chunk c into its stage buffer (chunks past the end
     // load valid, clamped addresses into a buffer nobody reads).  Gathered k:
@@ -329,12 +352,15 @@ __device__ __forceinline__ void gemm2_body(const typename P::Args& args, int log
         }
 #pragma unroll
         for (int j = 0; j < S::IA; ++j) {
-            if constexpr (S::KG) lds_load16(gathered(asrc[j], astr[j], arv[j]), buf + 4096 * j);
+            if constexpr (S::MU && G2MultiA<P>::value) lds_load16(gathered(asrc[j] + ishift, arv[j]), buf + 4096 * j);
+            else if constexpr (S::KG) lds_load16(gathered(asrc[j], arv[j]), buf + 4096 * j);
             else lds_load16(asrc[j] + aoff, buf + 4096 * j);
         }
 #pragma unroll
         for (int j = 0; j < S::IB; ++j) {
-            if constexpr (S::KG) lds_load16(gathered(bsrc[j], bstr[j], brv[j]), buf + S::A_BYTES + 4096 * j);
+            if constexpr (S::MU && !G2MultiA<P>::value)
+                lds_load16(gathered(bsrc[j] + ishift, brv[j]), buf + S::A_BYTES + 4096 * j);
+            else if constexpr (S::KG) lds_load16(gathered(bsrc[j], brv[j]), buf + S::A_BYTES + 4096 * j);
             else lds_load16(bsrc[j] + boff, buf + S::A_BYTES + 4096 * j);
         }
     };
@@ -389,7 +415,23 @@ __device__ __forceinline__ void gemm2_body(const typename P::Args& args, int log
             else f.a[i] = frag_m(ta, wm * S::WTM + i * 16, ks, std::integral_constant<int, MT / 8>{});
         }
     };
-    auto mfma_step = [&](const Frags& f) {
+    // several tiles: chunk of the tile being multiplied, chunks since a tile was stored
+    int cchunk = 0, since = STG;
+    constexpr int RB = S::ROW ? S::FN / S::WM : 1;  // row product: column blocks RB wm .. of this wave
+    float rsum[RB] = {};
+    auto mfma_step = [&](const Frags& f, int ks) {
+        if constexpr (S::ROW) {
+            const float4* z = reinterpret_cast<const float4*>(kf + cchunk * KC + ks + 8 * g);
+            const float4 z0 = z[0], z1 = z[1];
+            const float zv[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
+#pragma unroll
+            for (int j = 0; j < RB; ++j) {
+                float x[8];
+                frag8_to_f32<ST>(S::WM == 2 && wm ? f.b[(S::WM - 1) * RB + j] : f.b[j], x);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) rsum[j] = fmaf(zv[e], x[e], rsum[j]);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < S::FM; ++i)
 #pragma unroll
@@ -425,19 +467,65 @@ __device__ __forceinline__ void gemm2_body(const typename P::Args& args, int log
     // the accumulators to other registers.
     constexpr int KS = KC / 32, L = S::IA + S::IB;
     constexpr int UNROLL = STG * KS % 2 == 0 ? STG : 2 * STG;
-    if (nchunks > 0) {
+    // The table rows of the chunk after the one just issued (c): the next
+    // chunk, or with several tiles the first one of the next tile.
+    auto next_rows = [&](int c) {
+        if constexpr (S::MU) {
+            if (++ichunk == nchunks) {
+                ichunk = 0;
+                ishift += G2MultiA<P>::value ? MT : NT;
+            }
+            load_rows(ichunk);
+        } else {
+            load_rows(c + 1);
+        }
+    };
+    // Register epilogue of one tile (lane: M indices 32 p + 8 g .. + 7 of the
+    // wave's rows, column c16 of block j).
+    auto store_tile = [&](int mt0, int nt0) {
+        if constexpr (S::ER && !G2EpiAcc<P>::value) {
+#pragma unroll
+            for (int p = 0; p < S::FM / 2; ++p)
+#pragma unroll
+                for (int j = 0; j < S::FN; ++j) {
+                    float x[8];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        x[r] = acc[2 * p][j][r];
+                        x[4 + r] = acc[2 * p + 1][j][r];
+                    }
+                    P::store8(args, batch, mt0 + wm * S::WTM + 32 * p + 8 * g, nt0 + wn * S::WTN + 16 * j + c16, x);
+                }
+        }
+    };
+    // Gathered, K not a multiple of KC: chunk `cit` of a tile (0 .. nchunks - 1) has
+    // landed in stage buffer bidx; clears the rows past K of the last one.
+    auto clear_tail = [&](int cit, int bidx) {
+        if constexpr (S::KG) {
+            const int v = K - cit * KC;  // rows of the chunk that exist
+            if (v >= KC) return;
+            unsigned char* ta = smem + bidx * S::STAGE_BYTES;
+            for (int i = v * (MT / 8) + tid; i < KC * (MT / 8); i += 256)
+                *reinterpret_cast<uint4*>(ta + 16 * i) = make_uint4(0, 0, 0, 0);
+            for (int i = v * (NT / 8) + tid; i < KC * (NT / 8); i += 256)
+                *reinterpret_cast<uint4*>(ta + S::A_BYTES + 16 * i) = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+        }
+    };
+    if (total > 0) {
         Frags fr[2];
+        load_rows(0);
 #pragma unroll
         for (int s = 0; s < STG; ++s) {
-            if (s < nchunks) {
-                load_rows(s);
+            if (s < total) {
                 issue_buf(s, s);
+                next_rows(s);
             }
         }
-        load_rows(STG);
-        if (nchunks >= STG) wait_vmcnt<(STG - 1) * L>();
+        if (total >= STG) wait_vmcnt<(STG - 1) * L>();
         else wait_vmcnt<0>();
         __syncthreads();
+        clear_tail(0, 0);
         __builtin_amdgcn_sched_barrier(0);
         load_frags(fr[0], 0, 0);
         for (int c0 = 0;; c0 += UNROLL) {
@@ -452,21 +540,54 @@ __device__ __forceinline__ void gemm2_body(const typename P::Args& args, int log
                     } else {
                         if constexpr (G2AHook<P>::value)
                             P::a_tile_hook(args, m0, n0, smem + (u % STG) * S::STAGE_BYTES, tid, hook_state);
-                        if (c + STG <= nchunks) wait_vmcnt<(STG - 2) * L>();
-                        else wait_vmcnt<0>();
+                        if constexpr (S::MU) {
+                            // a tile stored within the last STAGES - 1 chunks: its
+                            // stores are younger than the loads of chunk c + 1
+                            if (c + STG > total) wait_vmcnt<0>();
+                            else if (++since < STG) wait_vmcnt<(STG - 2) * L + P::STORES>();
+                            else wait_vmcnt<(STG - 2) * L>();
+                        } else {
+                            if (c + STG <= total) wait_vmcnt<(STG - 2) * L>();
+                            else wait_vmcnt<0>();
+                        }
                         __syncthreads();
-                        if (c + STG < nchunks) {
+                        if (c + STG < total) {
                             issue_buf(c + STG, u % STG);
-                            load_rows(c + STG + 1);
+                            next_rows(c + STG);
+                        }
+                        if constexpr (S::KG) {
+                            const int nx = S::MU ? cchunk + 1 : c + 1;  // chunk c + 1 within its tile
+                            clear_tail(nx == nchunks ? 0 : nx, (u + 1) % STG);
                         }
                         __builtin_amdgcn_sched_barrier(0);
                         load_frags(fr[cur ^ 1], (u + 1) % STG, 0);
                     }
-                    mfma_step(fr[cur]);
+                    mfma_step(fr[cur], 32 * ks);
                     sched_mix<S::FM * S::FN, (P::A_KCONTIG ? 1 : 2) * S::FM + (P::B_KCONTIG ? 1 : 2) * S::FN>();
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                if (c + 1 == nchunks) {
+                if constexpr (S::MU) {
+                    if (++cchunk == nchunks) {
+                        cchunk = since = 0;
+                        mfma_drain();
+                        store_tile(m0, n0);
+                        if constexpr (S::ROW) {
+#pragma unroll
+                            for (int j = 0; j < RB; ++j) {
+                                const float v = rows4_sum(rsum[j]);  // the four k groups
+                                if (g == 0) P::store_row(args, batch, n0 + wn * S::WTN + 16 * (RB * wm + j) + c16, v);
+                                rsum[j] = 0.f;
+                            }
+                        }
+                        if constexpr (G2MultiA<P>::value) m0 += MT;
+                        else n0 += NT;
+#pragma unroll
+                        for (int i = 0; i < S::FM; ++i)
+#pragma unroll
+                            for (int j = 0; j < S::FN; ++j) acc[i][j] = zero4();
+                    }
+                }
+                if (c + 1 == total) {
                     mfma_drain();
                     goto pipeline_done;
                 }
@@ -481,19 +602,7 @@ pipeline_done:
         __syncthreads();
         P::template epi_acc<S>(args, batch, m0, n0, acc, wm, wn, tid, smem);
     } else if constexpr (S::ER) {
-        // lane: M indices 32 p + 8 g .. + 7 of the wave's rows, column c16 of block j
-#pragma unroll
-        for (int p = 0; p < S::FM / 2; ++p)
-#pragma unroll
-            for (int j = 0; j < S::FN; ++j) {
-                float x[8];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    x[r] = acc[2 * p][j][r];
-                    x[4 + r] = acc[2 * p + 1][j][r];
-                }
-                P::store8(args, batch, m0 + wm * S::WTM + 32 * p + 8 * g, n0 + wn * S::WTN + 16 * j + c16, x);
-            }
+        if constexpr (!S::MU) store_tile(m0, n0);
     } else {
         __syncthreads();
 

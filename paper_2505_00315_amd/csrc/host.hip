@@ -115,8 +115,8 @@ Layout make_layout(const mosa_shape* s) {
     L.dwr = bw.take(H > 0 && s->fixed_stride > 0 ? H * d * es : 0);  // dW^r sink without a router
     {
         const int dt = s->dtype == MOSA_BF16 ? kBF16 : kF32;
-        L.wpart = bw.take(wgrad_partial_bytes(dt, (int)B, (int)d, (int)H, (int)dh, (int)k, 1));
-        L.wpart_d = bw.take(wgrad_partial_bytes(dt, (int)B, (int)d, (int)Hd, (int)dh, (int)T, 0));
+        L.wpart = bw.take(wgrad_partial_bytes(dt, (int)B, (int)T, (int)d, (int)H, (int)dh, (int)k, 1));
+        L.wpart_d = bw.take(wgrad_partial_bytes(dt, (int)B, (int)T, (int)d, (int)Hd, (int)dh, (int)T, 0));
     }
     L.fwd_scratch = fw.total();
     L.scratch_total = fw.total() > bw.total() ? fw.total() : bw.total();
@@ -457,14 +457,14 @@ int mosa_backward_timed(const mosa_shape* s, const void* X, const mosa_weights* 
         e |= sm.mark("bwd_out_dense");
         // dW^O needs only dY and the saved A: it goes before the attention
         // backward, so that the chain's tail after it is short
-        e |= launch_wgrad(dt, X, dY, nullptr, Ad, dQKVd, nullptr, B, T, d, Hd, dh, T, g->dWq_d, g->dWk_d,
+        e |= launch_wgrad(dt, X, dY, nullptr, Ad, dQKVd, nullptr, nullptr, B, T, d, Hd, dh, T, g->dWq_d, g->dWk_d,
                           g->dWv_d, nullptr, g->dWo_d, wpd, 1, mk, ds);
         e |= launch_attn_bwd(dt, QKVd, dAd, lsed, Dd, B * Hd, T, dh, causal, s->window, dQKVd, nullptr, rope, 1, mk,
                              ds);
         // dQKV of the dense heads is complete: their dX GEMM may start on the
         // main stream once the MoSA heads' kernels are done
         if (ax && hipEventRecord(ax->mid, ds) != hipSuccess) e |= 1;
-        e |= launch_wgrad(dt, X, dY, nullptr, Ad, dQKVd, nullptr, B, T, d, Hd, dh, T, g->dWq_d, g->dWk_d,
+        e |= launch_wgrad(dt, X, dY, nullptr, Ad, dQKVd, nullptr, nullptr, B, T, d, Hd, dh, T, g->dWq_d, g->dWk_d,
                           g->dWv_d, nullptr, g->dWo_d, wpd, 0, mk, ds);
     }
     if (H > 0) {
@@ -479,7 +479,7 @@ int mosa_backward_timed(const mosa_shape* s, const void* X, const mosa_weights* 
         if (grouped < 0) e |= 1;
         if (grouped == 0) e |= sm.mark("bwd_proj");
         if (grouped == 1) {
-            e |= launch_wgrad(dt, X, dY, I, A, dQKV, dz16, B, T, d, H, dh, k, g->dWq, g->dWk, g->dWv, dWr, g->dWo,
+            e |= launch_wgrad(dt, X, dY, I, A, dQKV, dz16, dz, B, T, d, H, dh, k, g->dWq, g->dWk, g->dWv, dWr, g->dWo,
                               wpart, 2, mk, stream);
             e |= launch_dx_proj(dt, dQKV, dz, w->Wq, w->Wk, w->Wv, Wr, B, d, H, dh, k, dXs, stream);
             e |= sm.mark("dx_proj");

@@ -105,10 +105,10 @@ int launch_attn_bwd(int dtype, const void* QKV, const void* dA, const float* lse
 // "wgrad_o", each followed by "<name>_reduce" where partials are summed;
 // dense heads (I == nullptr) the same names with "_dense".
 int launch_wgrad(int dtype, const void* X, const void* dY, const int32_t* I, const void* A,
-                 const void* dQKV, const void* dz16, int B, int T, int d, int H, int dh, int n, void* dWq,
-                 void* dWk, void* dWv, void* dWr, void* dWo, float* part, int which, const Marker& mk,
+                 const void* dQKV, const void* dz16, const float* dz, int B, int T, int d, int H, int dh, int n,
+                 void* dWq, void* dWk, void* dWv, void* dWr, void* dWo, float* part, int which, const Marker& mk,
                  hipStream_t stream);
-size_t wgrad_partial_bytes(int dtype, int B, int d, int H, int dh, int n, int router);
+size_t wgrad_partial_bytes(int dtype, int B, int T, int d, int H, int dh, int n, int router);
 // The MoSA heads' dW^{Q,K,V,r}, dW^O and per-head dX rows (launch_dx_proj) in
 // one grouped launch; returns 1, launching nothing, where that does not apply.
 int launch_bwd_proj(int dtype, const void* X, const void* dY, const int32_t* I, const void* A, const void* dQKV,

@@ -6,7 +6,9 @@
 //            (the forward saved the rows r_r A_r already scaled)
 // Dense heads: the same with I = identity and r = 1 (no W^r).
 //
-// On the tiled MFMA engine the contraction index K is the row r, which is
+// bf16 storage: the gathered-row engine of gemm2.h, see WgradQkvPolicy2 below.
+// On the tiled MFMA engine of gemm.h (fp32, and bf16 past that one's reach) the
+// contraction index K is the row r, which is
 // contiguous in neither operand: both are staged with the engine's 8x8
 // register transpose.  wgrad_qkv: M = d, N = 3 dh (+ a 16-column block whose
 // first column is dz, so dW^r falls out of the same MFMAs), one workgroup per
@@ -47,6 +49,7 @@ struct WgradQkvPolicy {
         float* part;     // [S, H, d, NT] fp32 partial sums (S > 1)
         int T, d, H, n, R, mtiles, S, cps;
         FastDiv nd;
+        const float* dz; // [B, H, n] (the wide tiles)
     };
     struct ARef {};
     struct BRef {};
@@ -253,93 +256,93 @@ __global__ __launch_bounds__(256) void wgrad_o_reduce_kernel(const float* __rest
 // bf16 storage, MoSA heads: the multi-stage engine (gemm2.h) with the rows
 // gathered through an LDS table, k = r in order over the whole range (no
 // split: one workgroup owns its output tile, so the sums are reproducible
-// without partials).  Table entry of row r = (b, i): x = b T + I_r (the
-// token row of X or dY), y = (b H + h) n + i (the selected-row index), y = -1
-// past the last row (that operand then reads zeros).  The MFMA's A operand
-// is the one whose output index is contiguous in memory, interleaved so the
+// without partials).  Row r = (b, i): the table holds the offsets, in 16-byte
+// units, of token row b T + I_r (of X or dY) and of the selected row (b H + h) n
+// + i (of dQ | dK | dV or of the scaled attention rows).  The MFMA's A operand is
+// the one whose output index is contiguous in memory, interleaved so the
 // accumulators go straight to 16-byte stores.
-__device__ __forceinline__ int2 wgrad_k_row(const int32_t* I, const FastDiv& nd, int T, int H, int n, int h, int k,
-                                            int K) {
+template <class Args>
+__device__ __forceinline__ uint2 wgrad_k_row(const Args& a, int h, int k, int sel16) {
     int b, i;
-    fast_divmod(nd, min(k, K - 1), b, i);
-    const int ri = (b * H + h) * n + i;
-    return make_int2(b * T + I[ri], k < K ? ri : -1);
+    fast_divmod(a.nd, k, b, i);
+    const int ri = (b * a.H + h) * a.n + i;
+    return make_uint2((uint32_t)(b * a.T + a.I[ri]) * (uint32_t)(a.d / 8), (uint32_t)ri * (uint32_t)sel16);
 }
 
-// dW^{Q,K,V}_h and dW^r_h: M = the 3 dh + 64 output columns [dQ | dK | dV |
-// dz, 0 ...] (dz16 holds dz and 15 zeros; the rest reads the zero row),
-// N = 64 rows c of d per workgroup.
-template <int DH>
+// Several tiles of d per workgroup, in one pipeline (Args: S workgroups per
+// head, cps tiles each), where a tile has few chunks and that still leaves two
+// workgroups per CU: with 256 rows per head (8 chunks) a workgroup per tile
+// spent as long on its row table (a gather of I) and its first loads as on
+// the rest (128 heads, 256 rows, d 1024: 200.9 -> 193.8 us per training step).
+inline int wgrad_tiles_per_wg(int H, int tiles, int rows) {
+    return std::max(1, std::min({tiles, H * tiles / 512, 1024 / rows}));
+}
+
+// dW^{Q,K,V}_h and dW^r_h: M = the 3 dh columns [dQ | dK | dV], N = NT rows of d
+// per tile, dW^r as a row product beside the MFMAs (ROW, dz in fp32).  The
+// loop is bound by instruction issue and LDS as much as by its MFMAs: offsets
+// in the row table instead of row numbers (a multiplication and a select per
+// load less) and no 64-column block for the one column dz took the grouped
+// launch of 128 heads, 256 rows, d 1024 from 78.8 to 69.6 us, and the dense
+// heads' (4 heads, 8192 rows) from 31.5 to 25.0.  128 rows per tile halve the
+// LDS reads and the bytes moved into LDS per product: 69.6 -> 67.8 us, with 512
+// rows and 64 heads 63.4 -> 59.8.
+template <int DH, int NT_>
 struct WgradQkvPolicy2 {
     using ST = uint16_t;
-    static constexpr int MT = DH == 64 ? 256 : 128, NT = 64, KC = 32, WM = 2, WN = 2, STAGES = 3;
+    static constexpr int MT = 3 * DH, NT = NT_, KC = DH == 64 ? 32 : 64, WM = DH == 64 ? 2 : 1, WN = 4 / WM, STAGES = 3;
     static constexpr size_t EPI_LDS = 0;
     static constexpr bool A_KCONTIG = false, B_KCONTIG = false, KGATHER = true, A_INTERLEAVE = true, EPI_REGS = true;
     static constexpr int A_TAB = 1, B_TAB = 0, MIN_WAVES = 2;
+    static constexpr bool MULTI = true, MULTI_A = false, ROW = true;
+    static constexpr int STORES = 3 * (NT / WN / 16);  // 3 pairs of row blocks, each column block
     using Args = typename WgradQkvPolicy<ST, DH, true, true>::Args;
     __device__ static void tile(const Args& a, int logical, int& h, int& m0, int& n0) {
-        h = logical / a.mtiles;
+        h = logical / a.S;
         m0 = 0;
-        n0 = (logical % a.mtiles) * NT;
+        n0 = (logical % a.S) * a.cps * NT;
     }
+    __device__ static int tiles(const Args& a, int logical) { return min(a.cps, a.mtiles - (logical % a.S) * a.cps); }
     __device__ static int k_size(const Args& a, int) { return a.R; }
-    __device__ static int2 k_row(const Args& a, int h, int k, int K) {
-        return wgrad_k_row(a.I, a.nd, a.T, a.H, a.n, h, k, K);
+    __device__ static uint2 k_row(const Args& a, int h, int k) { return wgrad_k_row(a, h, k, 3 * DH / 8); }
+    __device__ static float k_f(const Args& a, int h, int k, int K) {
+        int b, i;
+        fast_divmod(a.nd, min(k, K - 1), b, i);
+        const float v = a.dz[(size_t)(b * a.H + h) * a.n + i];
+        return k < K ? v : 0.f;
     }
-    __device__ static void a_mlane(const Args& a, int, int m8, const ST*& base, uint32_t& stride) {
-        if (m8 < 3 * DH) {
-            base = a.dQKV + m8;
-            stride = 3 * DH;
-        } else if (m8 < 3 * DH + 16) {
-            base = a.dz16 + (m8 - 3 * DH);
-            stride = 16;
-        } else {
-            base = g2_zero;
-            stride = 0;
-        }
-    }
-    __device__ static void b_mlane(const Args& a, int, int n8, const ST*& base, uint32_t& stride) {
-        base = a.X + n8;
-        stride = a.d;
-    }
+    __device__ static const ST* a_mlane(const Args& a, int, int m8) { return a.dQKV + m8; }
+    __device__ static const ST* b_mlane(const Args& a, int, int n8) { return a.X + n8; }
     // columns m .. m + 7 of row c = n
     __device__ static void store8(const Args& a, int h, int m, int n, const float (&x)[8]) {
-        if (m < 3 * DH) {
-            ST* W = m < DH ? a.dWq : (m < 2 * DH ? a.dWk : a.dWv);
-            vec8_store<ST>(W + ((size_t)h * a.d + n) * DH + (m % DH), vec8_from_f32<ST>(x));
-        } else if (m == 3 * DH) {
-            st1<ST>(a.dWr + (size_t)h * a.d + n, x[0]);
-        }
+        ST* W = m < DH ? a.dWq : (m < 2 * DH ? a.dWk : a.dWv);
+        vec8_store<ST>(W + ((size_t)h * a.d + n) * DH + (m % DH), vec8_from_f32<ST>(x));
     }
+    __device__ static void store_row(const Args& a, int h, int n, float v) { st1<ST>(a.dWr + (size_t)h * a.d + n, v); }
 };
 
-// dW^O_h: M = 64 columns c of d per workgroup (dY rows), N = dh (the scaled
+// dW^O_h: M = MT columns c of d per tile (dY rows), N = dh (the scaled
 // attention rows).
-template <int DH>
+template <int DH, int MT_>
 struct WgradOPolicy2 {
     using ST = uint16_t;
-    static constexpr int MT = 64, NT = DH, KC = 64, WM = 2, WN = 2, STAGES = 4;
+    static constexpr int MT = MT_, NT = DH, KC = 64, WM = 2, WN = 2, STAGES = MT > 64 ? 3 : 4;
     static constexpr size_t EPI_LDS = 0;
     static constexpr bool A_KCONTIG = false, B_KCONTIG = false, KGATHER = true, A_INTERLEAVE = true, EPI_REGS = true;
     static constexpr int A_TAB = 0, B_TAB = 1;
+    static constexpr bool MULTI = true, MULTI_A = true;
+    static constexpr int STORES = (MT / 64) * (DH / 32);  // pairs of row blocks, column blocks
     using Args = typename WgradOPolicy<ST, DH, true>::Args;
     __device__ static void tile(const Args& a, int logical, int& h, int& m0, int& n0) {
-        h = logical / a.ntiles;
-        m0 = (logical % a.ntiles) * MT;
+        h = logical / a.S;
+        m0 = (logical % a.S) * a.cps * MT;
         n0 = 0;
     }
+    __device__ static int tiles(const Args& a, int logical) { return min(a.cps, a.ntiles - (logical % a.S) * a.cps); }
     __device__ static int k_size(const Args& a, int) { return a.R; }
-    __device__ static int2 k_row(const Args& a, int h, int k, int K) {
-        return wgrad_k_row(a.I, a.nd, a.T, a.H, a.n, h, k, K);
-    }
-    __device__ static void a_mlane(const Args& a, int, int m8, const ST*& base, uint32_t& stride) {
-        base = a.dY + m8;
-        stride = a.d;
-    }
-    __device__ static void b_mlane(const Args& a, int, int n8, const ST*& base, uint32_t& stride) {
-        base = a.A + n8;
-        stride = DH;
-    }
+    __device__ static uint2 k_row(const Args& a, int h, int k) { return wgrad_k_row(a, h, k, DH / 8); }
+    __device__ static const ST* a_mlane(const Args& a, int, int m8) { return a.dY + m8; }
+    __device__ static const ST* b_mlane(const Args& a, int, int n8) { return a.A + n8; }
     // columns c = m .. m + 7 of row e = n
     __device__ static void store8(const Args& a, int h, int m, int n, const float (&x)[8]) {
         vec8_store<ST>(a.dWo + ((size_t)h * DH + n) * a.d + m, vec8_from_f32<ST>(x));
@@ -349,48 +352,33 @@ struct WgradOPolicy2 {
 // Dense heads (bf16) on the same engine: R = B T rows split into S ranges of
 // up to 4096 rows (the row table), one fp32 partial tile per range, summed in
 // range order by the reduce kernels.  "batch" = h S + s.  Row r of range s:
-// x = r' = s KS + r (the row of X or dY), y = (b Hd + h) T + t (the head's
-// row), y = -1 past the range.
-__device__ __forceinline__ int2 wgrad_dense_k_row(const FastDiv& Td, int R, int KS, int T, int H, int batch, int S,
-                                                  int k, int K) {
-    const int h = batch / S, s = batch % S, r = min(s * KS + min(k, K - 1), R - 1);
+// row r' = s KS + r of X or dY and row (b Hd + h) T + t of the head.
+template <class Args>
+__device__ __forceinline__ uint2 wgrad_dense_k_row(const Args& a, int batch, int k, int sel16) {
+    const int r = min((batch % a.S) * a.cps + k, a.R - 1);
     int b, t;
-    fast_divmod(Td, r, b, t);
-    return make_int2(r, k < K ? (b * H + h) * T + t : -1);
+    fast_divmod(a.nd, r, b, t);
+    return make_uint2((uint32_t)r * (uint32_t)(a.d / 8),
+                      (uint32_t)((b * a.H + batch / a.S) * a.T + t) * (uint32_t)sel16);
 }
 
 template <int DH>
-struct WgradQkvDensePolicy2 : WgradQkvPolicy2<DH> {
+struct WgradQkvDensePolicy2 : WgradQkvPolicy2<DH, 64> {
     using ST = uint16_t;
-    static constexpr int MT = DH == 64 ? 192 : 128;  // [dQ | dK | dV] (DH 32: zero rows past 96)
-    using Args = typename WgradQkvPolicy2<DH>::Args;  // I unused, cps = rows per range
+    using Base = WgradQkvPolicy2<DH, 64>;
+    static constexpr bool MULTI = false, ROW = false;
+    using Args = typename Base::Args;  // I unused, cps = rows per range
     __device__ static void tile(const Args& a, int logical, int& batch, int& m0, int& n0) {
         // the heads of one (row range, column tile) side by side (its X block)
         const int h = logical % a.H, rest = logical / a.H;
         batch = h * a.S + rest / a.mtiles;  // h S + s
         m0 = 0;
-        n0 = (rest % a.mtiles) * WgradQkvPolicy2<DH>::NT;
+        n0 = (rest % a.mtiles) * Base::NT;
     }
     __device__ static int k_size(const Args& a, int batch) { return min(a.cps, a.R - (batch % a.S) * a.cps); }
-    __device__ static int2 k_row(const Args& a, int batch, int k, int K) {
-        return wgrad_dense_k_row(a.nd, a.R, a.cps, a.T, a.H, batch, a.S, k, K);
-    }
-    __device__ static void a_mlane(const Args& a, int, int m8, const ST*& base, uint32_t& stride) {
-        if (m8 < 3 * DH) {
-            base = a.dQKV + m8;
-            stride = 3 * DH;
-        } else {
-            base = g2_zero;
-            stride = 0;
-        }
-    }
-    __device__ static void b_mlane(const Args& a, int, int n8, const ST*& base, uint32_t& stride) {
-        base = a.X + n8;
-        stride = a.d;
-    }
+    __device__ static uint2 k_row(const Args& a, int batch, int k) { return wgrad_dense_k_row(a, batch, k, 3 * DH / 8); }
     // fp32 partial: part[s][h][c][3 DH], columns m .. m + 7 of row c = n
     __device__ static void store8(const Args& a, int batch, int m, int n, const float (&x)[8]) {
-        if (m >= 3 * DH) return;
         const int h = batch / a.S, s = batch % a.S;
         float* p = a.part + (((size_t)s * a.H + h) * a.d + n) * (3 * DH) + m;
         reinterpret_cast<float4*>(p)[0] = make_float4(x[0], x[1], x[2], x[3]);
@@ -399,20 +387,20 @@ struct WgradQkvDensePolicy2 : WgradQkvPolicy2<DH> {
 };
 
 template <int DH>
-struct WgradODensePolicy2 : WgradOPolicy2<DH> {
+struct WgradODensePolicy2 : WgradOPolicy2<DH, 64> {
     using ST = uint16_t;
-    using Args = typename WgradOPolicy2<DH>::Args;  // I unused, cps = rows per range
+    using Base = WgradOPolicy2<DH, 64>;
+    static constexpr bool MULTI = false;
+    using Args = typename Base::Args;  // I unused, cps = rows per range
     __device__ static void tile(const Args& a, int logical, int& batch, int& m0, int& n0) {
         // the heads of one (row range, column tile) side by side (its dY block)
         const int h = logical % a.H, rest = logical / a.H;
         batch = h * a.S + rest / a.ntiles;  // h S + s
-        m0 = (rest % a.ntiles) * WgradOPolicy2<DH>::MT;
+        m0 = (rest % a.ntiles) * Base::MT;
         n0 = 0;
     }
     __device__ static int k_size(const Args& a, int batch) { return min(a.cps, a.R - (batch % a.S) * a.cps); }
-    __device__ static int2 k_row(const Args& a, int batch, int k, int K) {
-        return wgrad_dense_k_row(a.nd, a.R, a.cps, a.T, a.H, batch, a.S, k, K);
-    }
+    __device__ static uint2 k_row(const Args& a, int batch, int k) { return wgrad_dense_k_row(a, batch, k, DH / 8); }
     // fp32 partial: part[s][h][e][c], columns c = m .. m + 7 of row e = n
     __device__ static void store8(const Args& a, int batch, int m, int n, const float (&x)[8]) {
         const int h = batch / a.S, s = batch % a.S;
@@ -436,11 +424,15 @@ inline int dense_ranges(int R, int tiles, int kc, int& rows) {
     return (R + rows - 1) / rows;
 }
 
-// Rows of the k-row table for a gathered range of R rows (0: not usable).
+// Rows of the k-row table for a gathered range of R rows (0: not usable: the
+// table is too long, or a tensor of `tokens` rows of d or `sel` rows of 3 dh
+// elements passes the 64 GB that the table's 32-bit offsets of 16-byte units
+// reach).
 template <class P2>
-int wgrad2_table_rows(int R, int d) {
+int wgrad2_table_rows(int R, int d, long long tokens, long long sel, int dh) {
     const int rows = (R + P2::KC - 1) / P2::KC * P2::KC;
     if (R <= 0 || rows > 4096 || d % 64 != 0) return 0;
+    if (tokens * d >= 1ll << 35 || sel * 3 * dh >= 1ll << 35) return 0;
     return rows;
 }
 
@@ -496,23 +488,24 @@ inline const char* wname(bool dense, int which, bool reduce) {
 }
 
 template <typename ST, int DH, bool ROUTER, bool GATHER>
-int run_qkv_t(const ST* X, const int32_t* I, const ST* dQKV, const ST* dz16, int B, int T, int d, int H, int n,
+int run_qkv_t(const ST* X, const int32_t* I, const ST* dQKV, const ST* dz16, const float* dz, int B, int T, int d, int H, int n,
               ST* dWq, ST* dWk, ST* dWv, ST* dWr, float* part, const Marker& mk, hipStream_t stream) {
     using P = WgradQkvPolicy<ST, DH, ROUTER, GATHER>;
     const bool dense = !GATHER;
     const int mtiles = (d + P::MT - 1) / P::MT, R = B * n;
     if constexpr (sizeof(ST) == 2 && ROUTER && GATHER) {
-        using P2 = WgradQkvPolicy2<DH>;
-        if (const int rows = wgrad2_table_rows<P2>(R, d)) {
-            typename P::Args a{X, I, dQKV, dz16, dWq, dWk, dWv, dWr, part, T, d, H, n, R, d / 64, 1, 0, make_fastdiv(n)};
-            return launch_gemm2<P2>(a, H * (d / 64), stream, rows) | mk(wname(dense, 0, false));
+        using P2 = WgradQkvPolicy2<DH, 64>;
+        if (const int rows = wgrad2_table_rows<P2>(R, d, (long long)B * T, (long long)R * H, DH)) {
+            const int tl = d / 64, per = wgrad_tiles_per_wg(H, tl, R), wgs = (tl + per - 1) / per;
+            typename P::Args a{X, I, dQKV, dz16, dWq, dWk, dWv, dWr, part, T, d, H, n, R, tl, wgs, per, make_fastdiv(n), dz};
+            return launch_gemm2<P2>(a, H * wgs, stream, rows) | mk(wname(dense, 0, false));
         }
     }
     if constexpr (sizeof(ST) == 2 && !ROUTER && !GATHER) {
         using P2 = WgradQkvDensePolicy2<DH>;
         int rows;
         const int S = dense_ranges(R, H * (d / 64), P2::KC, rows);
-        if (S > 0 && d % 64 == 0) {
+        if (S > 0 && d % 64 == 0 && (long long)R * d < 1ll << 35 && (long long)R * H * 3 * DH < 1ll << 35) {
             typename P2::Args a{X, I, dQKV, dz16, dWq, dWk, dWv, dWr, part, T, d, H, n, R, d / 64, S, rows,
                                 make_fastdiv(n)};
             int e = launch_gemm2<P2>(a, S * H * (d / 64), stream, rows);
@@ -549,11 +542,11 @@ int run_qkv_t(const ST* X, const int32_t* I, const ST* dQKV, const ST* dz16, int
 }
 
 template <typename ST, int DH>
-int run_qkv(const ST* X, const int32_t* I, const ST* dQKV, const ST* dz16, int B, int T, int d, int H, int n, ST* dWq,
+int run_qkv(const ST* X, const int32_t* I, const ST* dQKV, const ST* dz16, const float* dz, int B, int T, int d, int H, int n, ST* dWq,
             ST* dWk, ST* dWv, ST* dWr, float* part, const Marker& mk, hipStream_t stream) {
     if (I)  // MoSA heads: gathered rows and the router column
-        return run_qkv_t<ST, DH, true, true>(X, I, dQKV, dz16, B, T, d, H, n, dWq, dWk, dWv, dWr, part, mk, stream);
-    return run_qkv_t<ST, DH, false, false>(X, I, dQKV, dz16, B, T, d, H, n, dWq, dWk, dWv, dWr, part, mk, stream);
+        return run_qkv_t<ST, DH, true, true>(X, I, dQKV, dz16, dz, B, T, d, H, n, dWq, dWk, dWv, dWr, part, mk, stream);
+    return run_qkv_t<ST, DH, false, false>(X, I, dQKV, dz16, dz, B, T, d, H, n, dWq, dWk, dWv, dWr, part, mk, stream);
 }
 
 template <typename ST, int DH, bool GATHER>
@@ -563,17 +556,18 @@ int run_o_t(const ST* dY, const int32_t* I, const ST* A, int B, int T, int d, in
     const bool dense = !GATHER;
     const int R = B * n;
     if constexpr (sizeof(ST) == 2 && GATHER) {
-        using P2 = WgradOPolicy2<DH>;
-        if (const int rows = wgrad2_table_rows<P2>(R, d)) {
-            typename P::Args a{dY, I, A, dWo, part, T, d, H, n, R, d / 64, 1, 0, make_fastdiv(n)};
-            return launch_gemm2<P2>(a, H * (d / 64), stream, rows) | mk(wname(dense, 1, false));
+        using P2 = WgradOPolicy2<DH, 64>;
+        if (const int rows = wgrad2_table_rows<P2>(R, d, (long long)B * T, (long long)R * H, DH)) {
+            const int tl = d / 64, per = wgrad_tiles_per_wg(H, tl, R), wgs = (tl + per - 1) / per;
+            typename P::Args a{dY, I, A, dWo, part, T, d, H, n, R, tl, wgs, per, make_fastdiv(n)};
+            return launch_gemm2<P2>(a, H * wgs, stream, rows) | mk(wname(dense, 1, false));
         }
     }
     if constexpr (sizeof(ST) == 2 && !GATHER) {
         using P2 = WgradODensePolicy2<DH>;
         int rows;
         const int S = dense_ranges(R, H * (d / 64), P2::KC, rows);
-        if (S > 0 && d % 64 == 0) {
+        if (S > 0 && d % 64 == 0 && (long long)R * d < 1ll << 35 && (long long)R * H * 3 * DH < 1ll << 35) {
             typename P2::Args a{dY, I, A, dWo, part, T, d, H, n, R, d / 64, S, rows, make_fastdiv(n)};
             int e = launch_gemm2<P2>(a, S * H * (d / 64), stream, rows);
             e |= mk(wname(dense, 1, false));
@@ -620,48 +614,68 @@ int run_o(const ST* dY, const int32_t* I, const ST* A, int B, int T, int d, int 
 // engine (the two kinds of workgroups share the CUs); 1: not applicable.
 template <int DH>
 int run_both(const uint16_t* X, const uint16_t* dY, const int32_t* I, const uint16_t* A, const uint16_t* dQKV,
-             const uint16_t* dz16, int B, int T, int d, int H, int n, uint16_t* dWq, uint16_t* dWk, uint16_t* dWv,
+             const uint16_t* dz16, const float* dz, int B, int T, int d, int H, int n, uint16_t* dWq, uint16_t* dWk, uint16_t* dWv,
              uint16_t* dWr, uint16_t* dWo, hipStream_t stream) {
     using ST = uint16_t;
-    using PQ = WgradQkvPolicy2<DH>;
-    using PO = WgradOPolicy2<DH>;
+    using PQ = WgradQkvPolicy2<DH, 64>;
+    using PO = WgradOPolicy2<DH, 64>;
     const int R = B * n;
-    const int rq = wgrad2_table_rows<PQ>(R, d), ro = wgrad2_table_rows<PO>(R, d);
+    const int rq = wgrad2_table_rows<PQ>(R, d, (long long)B * T, (long long)R * H, DH), ro = wgrad2_table_rows<PO>(R, d, (long long)B * T, (long long)R * H, DH);
     if (!rq || !ro) return 1;
-    typename PQ::Args aq{X, I, dQKV, dz16, dWq, dWk, dWv, dWr, nullptr, T, d, H, n, R, d / 64, 1, 0, make_fastdiv(n)};
-    typename PO::Args ao{dY, I, A, dWo, nullptr, T, d, H, n, R, d / 64, 1, 0, make_fastdiv(n)};
-    const int e = launch_gemm2_dual<PQ, PO>(aq, H * (d / 64), rq, ao, H * (d / 64), ro, stream);
+    const int tl = d / 64, per = wgrad_tiles_per_wg(H, tl, R), wgs = (tl + per - 1) / per;
+    typename PQ::Args aq{X, I, dQKV, dz16, dWq, dWk, dWv, dWr, nullptr, T, d, H, n, R, tl, wgs, per, make_fastdiv(n), dz};
+    typename PO::Args ao{dY, I, A, dWo, nullptr, T, d, H, n, R, tl, wgs, per, make_fastdiv(n)};
+    const int e = launch_gemm2_dual<PQ, PO>(aq, H * wgs, rq, ao, H * wgs, ro, stream);
     return e == -1 ? 1 : e;  // a shape the grouped launch cannot take falls back to two launches
 }
 
 // The three products after the attention backward in one launch: dW^{Q,K,V,r},
-// dW^O and the per-head dX rows; 1: not applicable.
+// dW^O and the per-head dX rows; 1: not applicable.  PQ, PO: the tiles of the
+// two weight gradients.
+template <class PQ, class PO, int DH>
+int run_bwd_proj_t(const uint16_t* X, const uint16_t* dY, const int32_t* I, const uint16_t* A, const uint16_t* dQKV,
+                   const uint16_t* dz16, const float* dz, const uint16_t* Wq, const uint16_t* Wk, const uint16_t* Wv,
+                   const uint16_t* Wr, int B, int T, int d, int H, int n, uint16_t* dWq, uint16_t* dWk, uint16_t* dWv,
+                   uint16_t* dWr, uint16_t* dWo, uint16_t* dXs, hipStream_t stream) {
+    using PX = DxProjRowPolicy<DH>;
+    const int R = B * n;
+    const int rq = wgrad2_table_rows<PQ>(R, d, (long long)B * T, (long long)R * H, DH), ro = wgrad2_table_rows<PO>(R, d, (long long)B * T, (long long)R * H, DH);
+    typename PX::Args ax;
+    int nx;
+    if (!rq || !ro || !dx_row_args<DH>(dQKV, dz, Wq, Wk, Wv, Wr, B, d, H, n, dXs, ax, nx)) return 1;
+    const int tq = d / PQ::NT, pq = wgrad_tiles_per_wg(H, tq, rq), wq = (tq + pq - 1) / pq;
+    const int to = d / PO::MT, po = wgrad_tiles_per_wg(H, to, ro), wo = (to + po - 1) / po;
+    typename PQ::Args aq{X, I, dQKV, dz16, dWq, dWk, dWv, dWr, nullptr, T, d, H, n, R, tq, wq, pq, make_fastdiv(n), dz};
+    typename PO::Args ao{dY, I, A, dWo, nullptr, T, d, H, n, R, to, wo, po, make_fastdiv(n)};
+    return launch_group3<Gemm2Job<PQ>, Gemm2Job<PO>, RowGemmJob<PX>>(
+        aq, H * wq, Gemm2Job<PQ>::lds(rq), ao, H * wo, Gemm2Job<PO>::lds(ro), ax, nx,
+        RowGemmJob<PX>::lds(0), stream);
+}
+
 template <int DH>
 int run_bwd_proj(const uint16_t* X, const uint16_t* dY, const int32_t* I, const uint16_t* A, const uint16_t* dQKV,
                  const uint16_t* dz16, const float* dz, const uint16_t* Wq, const uint16_t* Wk, const uint16_t* Wv,
                  const uint16_t* Wr, int B, int T, int d, int H, int n, uint16_t* dWq, uint16_t* dWk, uint16_t* dWv,
                  uint16_t* dWr, uint16_t* dWo, uint16_t* dXs, hipStream_t stream) {
-    using PQ = WgradQkvPolicy2<DH>;
-    using PO = WgradOPolicy2<DH>;
-    using PX = DxProjRowPolicy<DH>;
-    const int R = B * n;
-    const int rq = wgrad2_table_rows<PQ>(R, d), ro = wgrad2_table_rows<PO>(R, d);
-    typename PX::Args ax;
-    int nx;
-    if (!rq || !ro || !dx_row_args<DH>(dQKV, dz, Wq, Wk, Wv, Wr, B, d, H, n, dXs, ax, nx)) return 1;
-    typename PQ::Args aq{X, I, dQKV, dz16, dWq, dWk, dWv, dWr, nullptr, T, d, H, n, R, d / 64, 1, 0, make_fastdiv(n)};
-    typename PO::Args ao{dY, I, A, dWo, nullptr, T, d, H, n, R, d / 64, 1, 0, make_fastdiv(n)};
-    return launch_group3<Gemm2Job<PQ>, Gemm2Job<PO>, RowGemmJob<PX>>(
-        aq, H * (d / 64), Gemm2Job<PQ>::lds(rq), ao, H * (d / 64), Gemm2Job<PO>::lds(ro), ax, nx,
-        RowGemmJob<PX>::lds(0), stream);
+    auto go = [&](auto f) {
+        return f(X, dY, I, A, dQKV, dz16, dz, Wq, Wk, Wv, Wr, B, T, d, H, n, dWq, dWk, dWv, dWr, dWo, dXs, stream);
+    };
+    // 128-column tiles where they still give every CU one
+    if constexpr (DH == 64) {
+        if (d % 128 == 0 && H * (d / 128) >= kFullChip)
+            return go(run_bwd_proj_t<WgradQkvPolicy2<DH, 128>, WgradOPolicy2<DH, 128>, DH>);
+    }
+    return go(run_bwd_proj_t<WgradQkvPolicy2<DH, 64>, WgradOPolicy2<DH, 64>, DH>);
 }
 
 // Bytes of fp32 partial sums the two launches of one head group need.
 template <typename ST, int DH>
-size_t partial_bytes(int B, int d, int H, int n, bool router) {
+size_t partial_bytes(int B, int T, int d, int H, int n, bool router) {
     const int R = B * n;
     if constexpr (sizeof(ST) == 2) {  // MoSA heads on the gathered-row engine: no partials
-        if (router && wgrad2_table_rows<WgradQkvPolicy2<DH>>(R, d) && wgrad2_table_rows<WgradOPolicy2<DH>>(R, d))
+        // (a tensor past the table's reach takes the fallback, whose partials are kept room for)
+        if (router && wgrad2_table_rows<WgradQkvPolicy2<DH, 64>>(R, d, (long long)B * T, (long long)R * H, DH) &&
+            wgrad2_table_rows<WgradOPolicy2<DH, 64>>(R, d, (long long)B * T, (long long)R * H, DH))
             return 0;
     }
     // (the plans do not depend on GATHER)
@@ -685,28 +699,28 @@ size_t partial_bytes(int B, int d, int H, int n, bool router) {
 }  // namespace
 
 int launch_wgrad(int dtype, const void* X, const void* dY, const int32_t* I, const void* A, const void* dQKV,
-                 const void* dz16, int B, int T, int d, int H, int dh, int n, void* dWq, void* dWk, void* dWv,
-                 void* dWr, void* dWo, float* part, int which, const Marker& mk, hipStream_t stream) {
+                 const void* dz16, const float* dz, int B, int T, int d, int H, int dh, int n, void* dWq, void* dWk,
+                 void* dWv, void* dWr, void* dWo, float* part, int which, const Marker& mk, hipStream_t stream) {
     if (H == 0) return 0;
     if (which == 2) {
         // both: one launch on the gathered-row engine where it applies
         if (dtype == kBF16 && I) {
             using ST = uint16_t;
             auto both = dh == 64 ? run_both<64> : run_both<32>;
-            const int e = both((const ST*)X, (const ST*)dY, I, (const ST*)A, (const ST*)dQKV, (const ST*)dz16, B, T, d,
+            const int e = both((const ST*)X, (const ST*)dY, I, (const ST*)A, (const ST*)dQKV, (const ST*)dz16, dz, B, T, d,
                                H, n, (ST*)dWq, (ST*)dWk, (ST*)dWv, (ST*)dWr, (ST*)dWo, stream);
             if (e != 1) return e | mk("wgrad");
         }
-        const int e0 = launch_wgrad(dtype, X, dY, I, A, dQKV, dz16, B, T, d, H, dh, n, dWq, dWk, dWv, dWr, dWo, part,
+        const int e0 = launch_wgrad(dtype, X, dY, I, A, dQKV, dz16, dz, B, T, d, H, dh, n, dWq, dWk, dWv, dWr, dWo, part,
                                     0, mk, stream);
-        return e0 | launch_wgrad(dtype, X, dY, I, A, dQKV, dz16, B, T, d, H, dh, n, dWq, dWk, dWv, dWr, dWo, part, 1,
+        return e0 | launch_wgrad(dtype, X, dY, I, A, dQKV, dz16, dz, B, T, d, H, dh, n, dWq, dWk, dWv, dWr, dWo, part, 1,
                                  mk, stream);
     }
     if (dtype == kBF16) {
         using ST = uint16_t;
         if (which == 0) {
             auto f = dh == 64 ? run_qkv<ST, 64> : run_qkv<ST, 32>;
-            return f((const ST*)X, I, (const ST*)dQKV, (const ST*)dz16, B, T, d, H, n, (ST*)dWq, (ST*)dWk, (ST*)dWv,
+            return f((const ST*)X, I, (const ST*)dQKV, (const ST*)dz16, dz, B, T, d, H, n, (ST*)dWq, (ST*)dWk, (ST*)dWv,
                      (ST*)dWr, part, mk, stream);
         }
         auto f = dh == 64 ? run_o<ST, 64> : run_o<ST, 32>;
@@ -715,7 +729,7 @@ int launch_wgrad(int dtype, const void* X, const void* dY, const int32_t* I, con
     using ST = float;
     if (which == 0) {
         auto f = dh == 64 ? run_qkv<ST, 64> : run_qkv<ST, 32>;
-        return f((const ST*)X, I, (const ST*)dQKV, (const ST*)dz16, B, T, d, H, n, (ST*)dWq, (ST*)dWk, (ST*)dWv,
+        return f((const ST*)X, I, (const ST*)dQKV, (const ST*)dz16, dz, B, T, d, H, n, (ST*)dWq, (ST*)dWk, (ST*)dWv,
                  (ST*)dWr, part, mk, stream);
     }
     auto f = dh == 64 ? run_o<ST, 64> : run_o<ST, 32>;
@@ -738,12 +752,12 @@ int launch_bwd_proj(int dtype, const void* X, const void* dY, const int32_t* I, 
              (ST*)dWo, (ST*)dXs, stream);
 }
 
-size_t wgrad_partial_bytes(int dtype, int B, int d, int H, int dh, int n, int router) {
+size_t wgrad_partial_bytes(int dtype, int B, int T, int d, int H, int dh, int n, int router) {
     if (H == 0 || n == 0) return 0;
     if (dtype == kBF16)
-        return dh == 64 ? partial_bytes<uint16_t, 64>(B, d, H, n, router)
-                        : partial_bytes<uint16_t, 32>(B, d, H, n, router);
-    return dh == 64 ? partial_bytes<float, 64>(B, d, H, n, router) : partial_bytes<float, 32>(B, d, H, n, router);
+        return dh == 64 ? partial_bytes<uint16_t, 64>(B, T, d, H, n, router)
+                        : partial_bytes<uint16_t, 32>(B, T, d, H, n, router);
+    return dh == 64 ? partial_bytes<float, 64>(B, T, d, H, n, router) : partial_bytes<float, 32>(B, T, d, H, n, router);
 }
 
 }  // namespace mosa
