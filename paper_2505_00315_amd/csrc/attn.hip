@@ -439,16 +439,18 @@ __global__ __launch_bounds__(512) void attn_fwd_lds_kernel(const uint16_t* __res
 
 // ---------------------------------------------------------------------------
 // bf16 with 64-wide heads, n > 128 or a local window: flash-style attention
-// with 32 queries per wave -- two 16-query MFMA column blocks that share every
-// K and V fragment read from LDS, so each LDS byte feeds twice the MFMA work
-// of a 16-query wave -- and 4 waves, 128 queries, per workgroup.  Keys go in
+// with QN blocks of 16 queries per wave and 4 waves, 64 QN queries, per
+// workgroup.  With QN = 2 the two MFMA column blocks share every K and V
+// fragment read from LDS; QN = 1 gives twice the workgroups, half as long (see
+// fa_geom).  Keys go in
 // tiles of 64 through a 4-stage LDS ring filled by direct global->LDS loads
 // (K rows with XOR-permuted 16-byte units for ds_read_b128, V rows with the
-// vt_swz permutation for transposed reads), 3 tiles in flight.  S^T = K Q^T
+// vt_swz permutation for transposed reads), 3 tiles in flight (QN = 1: 2
+// stages, one tile in flight per workgroup).  S^T = K Q^T
 // (lane = query), online softmax in log2 units, O^T += V^T P^T 32 keys per
 // MFMA from the P^T registers.
 //
-// A (b, h) has nqb blocks of 128 queries; block qb covers key tiles
+// A (b, h) has nqb blocks of 64 QN queries; block qb covers key tiles
 // [lo, lo + nt) (causal: up to its last query; local window: from its first
 // query's window start).  Blocks are taken heaviest first, and a block of more
 // than `tps` tiles is cut into splits of tps tiles: each split writes an fp32
@@ -456,16 +458,24 @@ __global__ __launch_bounds__(512) void attn_fwd_lds_kernel(const uint16_t* __res
 // attn_fa_merge_kernel combines the splits of a block in split order, so the
 // result is reproducible.  Unsplit blocks write A and lse directly.
 // ---------------------------------------------------------------------------
-constexpr int kFaQB = 128, kFaKB = 64, kFaStages = 4;
-constexpr int kFaPart = kFaQB * 64 + 2 * kFaQB;  // floats per partial: O [128][64], m [128], l [128]
+constexpr int kFaKB = 64;
+// Ring stages: 64 KB for QN = 2; for QN = 1 32 KB each, so that the two
+// workgroups that a CU then holds leave a kernel of another stream the room it
+// had beside one of QN = 2 (with 4 stages a layer of 256 MoSA heads, k = 16,
+// and 4 dense ones, d 1024, T = 1024, B = 8 took 373 us, with 2 stages 358).
+__host__ __device__ constexpr int fa_stages(int qn) { return qn == 1 ? 2 : 4; }
 
 struct FaGeom {
-    int n, causal, win, lb, nqb, tps, wph;  // wph: workgroups per (b, h)
+    int n, causal, win, lb, qn, nqb, tps, wph;  // qn: QN; wph: workgroups per (b, h)
 };
+__host__ __device__ inline int fa_qb_rows(const FaGeom& G) { return 64 * G.qn; }
+// Only blocks of 128 queries are split (fa_geom).
+constexpr int kFaSplitQB = 128;
+constexpr int kFaPart = kFaSplitQB * 64 + 2 * kFaSplitQB;  // floats per partial: O [128][64], m [128], l [128]
 
 __host__ __device__ inline void fa_range(const FaGeom& G, int qb, int& lo, int& nt) {
-    const int q0 = qb * kFaQB;
-    const int hi = G.causal ? min(G.n, q0 + kFaQB) : G.n;
+    const int q0 = qb * fa_qb_rows(G);
+    const int hi = G.causal ? min(G.n, q0 + fa_qb_rows(G)) : G.n;
     lo = G.win ? (max(0, q0 - G.lb) / kFaKB) * kFaKB : 0;
     nt = (hi - lo + kFaKB - 1) / kFaKB;
 }
@@ -477,21 +487,38 @@ __host__ __device__ inline int fa_nsplit(const FaGeom& G, int qb) {
 // query block at position p of the launch order (causal: heaviest first)
 __host__ __device__ inline int fa_qb_at(const FaGeom& G, int p) { return G.causal ? G.nqb - 1 - p : p; }
 
-template <bool WIN>
+template <bool WIN, int QN>
 __global__ __launch_bounds__(256) void attn_fa_fwd_kernel(const uint16_t* __restrict__ QKV, FaGeom G, float scale,
                                                           const float* __restrict__ rw, uint16_t* __restrict__ A,
                                                           float* __restrict__ lse, float* __restrict__ part) {
     using ST = uint16_t;
-    constexpr int DH = 64, RS = 3 * DH, U = DH / 8, KB = kFaKB, QB = kFaQB, STG = kFaStages;
+    constexpr int DH = 64, RS = 3 * DH, U = DH / 8, KB = kFaKB, QB = 64 * QN, STG = fa_stages(QN);
     constexpr int TILE = KB * DH * 2, STAGE = 2 * TILE;  // K then V
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, c16 = lane & 15;
-    const int logical = xcd_logical_id(blockIdx.x, gridDim.x);  // the blocks of a (b, h) share an XCD
-    const int bh = logical / G.wph, j = logical % G.wph;
+    // The blocks of a (b, h) share an XCD.  Where every XCD has whole heads
+    // and no block is split, its blocks are ranked heaviest first over its
+    // heads and dealt to its 32 CUs in rounds, every second full round in
+    // reverse, so that a CU's blocks add up to about the same work (forward of
+    // 16 dense heads, B = 32, T = 1024: 379 -> 358 us; B = 4, T = 4096: 426 ->
+    // 395; 8 heads, B = 4, T = 1000 with QN = 1: 39.6 -> 37.0).
+    int bh, j;
+    const int wgs = gridDim.x;
+    if (G.wph == G.nqb && wgs % 8 == 0 && (wgs / G.wph) % 8 == 0) {
+        const int r = blockIdx.x / 8, per = wgs / 8, nx = per / G.wph, m = r / 32;
+        const int s = (m & 1) && 32 * (m + 1) <= per ? 32 * m + 31 - r % 32 : r;
+        bh = (blockIdx.x % 8) * nx + s % nx;
+        j = s / nx;
+    } else {
+        const int logical = xcd_logical_id(blockIdx.x, wgs);
+        bh = logical / G.wph;
+        j = logical % G.wph;
+    }
     // (block, split) of this workgroup
-    int qb = 0, sp = 0, first = 0;
-    for (int p = 0, acc = 0; p < G.nqb; ++p) {
+    const bool whole = G.wph == G.nqb;  // no block is split
+    int qb = fa_qb_at(G, j), sp = 0, first = j;
+    for (int p = 0, acc = 0; !whole && p < G.nqb; ++p) {
         const int q = fa_qb_at(G, p), ns = fa_nsplit(G, q);
         if (j < acc + ns) {
             qb = q;
@@ -505,23 +532,23 @@ __global__ __launch_bounds__(256) void attn_fa_fwd_kernel(const uint16_t* __rest
     fa_range(G, qb, lo, nt);
     const int nsplit = (nt + G.tps - 1) / G.tps;
     const int tbeg = sp * G.tps, tend = min(nt, tbeg + G.tps), ntile = tend - tbeg;
-    const int n = G.n, q0 = qb * QB, wq0 = q0 + 32 * wave;
+    const int n = G.n, q0 = qb * QB, wq0 = q0 + 16 * QN * wave;
     const ST* Qp = QKV + (size_t)bh * n * RS;
     const ST* Kp = Qp + DH;
     const ST* Vp = Qp + 2 * DH;
 
     // query fragments (B operand of S^T = K Q^T): query wq0 + 16 qs + c16,
     // d_head 32 st + 8 g .. + 7 (rows past n clamped; never written)
-    Frag8<ST> qf[2][2];
+    Frag8<ST> qf[QN][2];
 #pragma unroll
-    for (int qs = 0; qs < 2; ++qs)
+    for (int qs = 0; qs < QN; ++qs)
 #pragma unroll
         for (int st = 0; st < 2; ++st)
             qf[qs][st] = frag8_load<ST>(Qp + (size_t)min(wq0 + 16 * qs + c16, n - 1) * RS + 32 * st + 8 * g);
     // Take the query rows now: a first use inside the pipeline would make the
     // compiler wait for every load in flight there, the next tiles' included.
 #pragma unroll
-    for (int qs = 0; qs < 2; ++qs)
+    for (int qs = 0; qs < QN; ++qs)
 #pragma unroll
         for (int st = 0; st < 2; ++st) asm volatile("" : "+v"(qf[qs][st].v));
 
@@ -551,12 +578,15 @@ __global__ __launch_bounds__(256) void attn_fa_fwd_kernel(const uint16_t* __rest
     };
 
     const float c2 = scale * 1.44269504088896341f;  // scores in log2 units
-    float m_run[2] = {-__builtin_inff(), -__builtin_inff()}, l_run[2] = {0.f, 0.f};
-    f32x4 o[2][DH / 16];
+    float m_run[QN], l_run[QN];
+    f32x4 o[QN][DH / 16];
 #pragma unroll
-    for (int qs = 0; qs < 2; ++qs)
+    for (int qs = 0; qs < QN; ++qs) {
+        m_run[qs] = -__builtin_inff();
+        l_run[qs] = 0.f;
 #pragma unroll
         for (int db = 0; db < DH / 16; ++db) o[qs][db] = zero4();
+    }
 
 #pragma unroll
     for (int s0 = 0; s0 < STG - 1; ++s0) issue(s0, s0);
@@ -607,24 +637,24 @@ __global__ __launch_bounds__(256) void attn_fa_fwd_kernel(const uint16_t* __rest
         // S^T for 4 blocks of 16 keys: lane = query c16, rows = keys 16 sb + 4 g
         // + i; the two d_head halves in separate passes, so that no MFMA waits
         // for the one just before it
-        f32x4 s[2][4];
+        f32x4 s[QN][4];
 #pragma unroll
         for (int sb = 0; sb < 4; ++sb)
 #pragma unroll
-            for (int qs = 0; qs < 2; ++qs) {
+            for (int qs = 0; qs < QN; ++qs) {
                 s[qs][sb] = zero4();
                 mma8(s[qs][sb], kf[sb][0], qf[qs][0]);
             }
 #pragma unroll
         for (int sb = 0; sb < 4; ++sb)
 #pragma unroll
-            for (int qs = 0; qs < 2; ++qs) mma8(s[qs][sb], kf[sb][1], qf[qs][1]);
+            for (int qs = 0; qs < QN; ++qs) mma8(s[qs][sb], kf[sb][1], qf[qs][1]);
         // a tile needs the per-element mask where it reaches past a query of
         // this wave (causal), past n, or before a query's window
-        const bool need = (G.causal && j0 + KB - 1 > wq0) || j0 + KB > n || (WIN && wq0 + 31 - j0 > G.lb);
+        const bool need = (G.causal && j0 + KB - 1 > wq0) || j0 + KB > n || (WIN && wq0 + 16 * QN - 1 - j0 > G.lb);
         if (need) {  // one wave-uniform branch; selects without branches inside
 #pragma unroll
-            for (int qs = 0; qs < 2; ++qs) {
+            for (int qs = 0; qs < QN; ++qs) {
                 const int q = wq0 + 16 * qs + c16;
 #pragma unroll
                 for (int sb = 0; sb < 4; ++sb)
@@ -638,9 +668,9 @@ __global__ __launch_bounds__(256) void attn_fa_fwd_kernel(const uint16_t* __rest
                     }
             }
         }
-        float p[2][4][4];
+        float p[QN][4][4];
 #pragma unroll
-        for (int qs = 0; qs < 2; ++qs) {
+        for (int qs = 0; qs < QN; ++qs) {
             float mloc = -__builtin_inff();  // over the raw scores (the scale is positive)
 #pragma unroll
             for (int sb = 0; sb < 4; ++sb)
@@ -677,9 +707,9 @@ __global__ __launch_bounds__(256) void attn_fa_fwd_kernel(const uint16_t* __rest
         // block 2u, slots 4..7 = the same of block 2u+1 (V^T read in that order)
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            Frag8<ST> pf[2];
+            Frag8<ST> pf[QN];
 #pragma unroll
-            for (int qs = 0; qs < 2; ++qs) {
+            for (int qs = 0; qs < QN; ++qs) {
                 const float pv[8] = {p[qs][2 * u][0],     p[qs][2 * u][1],     p[qs][2 * u][2],     p[qs][2 * u][3],
                                      p[qs][2 * u + 1][0], p[qs][2 * u + 1][1], p[qs][2 * u + 1][2], p[qs][2 * u + 1][3]};
                 pf[qs] = frag8_from<ST>(pv);
@@ -691,7 +721,7 @@ __global__ __launch_bounds__(256) void attn_fa_fwd_kernel(const uint16_t* __rest
                 Frag8<ST> vf;
                 vf.v = __builtin_bit_cast(bf16x8, vt[u][db]);
 #pragma unroll
-                for (int qs = 0; qs < 2; ++qs) mma8(o[qs][db], vf, pf[qs]);
+                for (int qs = 0; qs < QN; ++qs) mma8(o[qs][db], vf, pf[qs]);
             }
         }
     };
@@ -709,12 +739,12 @@ __global__ __launch_bounds__(256) void attn_fa_fwd_kernel(const uint16_t* __rest
     wait_vmcnt<0>();   // the trailing (clamped) loads still write into the ring
     __syncthreads();
 
-    if (nsplit > 1) {
+    if (QN == 2 && nsplit > 1) {
         // fp32 partial of this split: O^T rows straight from the accumulators
         float* pp = part + ((size_t)bh * G.wph + first + sp) * kFaPart;
 #pragma unroll
-        for (int qs = 0; qs < 2; ++qs) {
-            const int ql = 32 * wave + 16 * qs + c16;
+        for (int qs = 0; qs < QN; ++qs) {
+            const int ql = 16 * QN * wave + 16 * qs + c16;
 #pragma unroll
             for (int db = 0; db < DH / 16; ++db)
                 *reinterpret_cast<float4*>(pp + ql * DH + 16 * db + 4 * g) =
@@ -728,9 +758,9 @@ __global__ __launch_bounds__(256) void attn_fa_fwd_kernel(const uint16_t* __rest
     }
     // whole block: A = r O / l through LDS to 16-byte row stores, lse = m ln 2 + log l
     constexpr int LDO = DH + 8;
-    ST* Os = reinterpret_cast<ST*>(smem) + wave * 32 * LDO;
+    ST* Os = reinterpret_cast<ST*>(smem) + wave * 16 * QN * LDO;
 #pragma unroll
-    for (int qs = 0; qs < 2; ++qs) {
+    for (int qs = 0; qs < QN; ++qs) {
         const int q = wq0 + 16 * qs + c16;
         const float inv = (rw && q < n ? rw[(size_t)bh * n + q] : 1.f) / l_run[qs];
 #pragma unroll
@@ -743,7 +773,7 @@ __global__ __launch_bounds__(256) void attn_fa_fwd_kernel(const uint16_t* __rest
     }
     __syncthreads();
 #pragma unroll
-    for (int e = lane; e < 32 * U; e += 64) {
+    for (int e = lane; e < 16 * QN * U; e += 64) {
         const int r = e / U, dc = (e % U) * 8;
         if (wq0 + r < n)
             *reinterpret_cast<uint4*>(A + ((size_t)bh * n + wq0 + r) * DH + dc) =
@@ -757,7 +787,7 @@ __global__ __launch_bounds__(256) void attn_fa_fwd_kernel(const uint16_t* __rest
 __global__ __launch_bounds__(128) void attn_fa_merge_kernel(FaGeom G, const float* __restrict__ part,
                                                             const float* __restrict__ rw, uint16_t* __restrict__ A,
                                                             float* __restrict__ lse) {
-    constexpr int DH = 64, QB = kFaQB, NC = DH / 4;
+    constexpr int DH = 64, QB = kFaSplitQB, NC = DH / 4;
     const int cq = blockIdx.x & 3, bp = blockIdx.x >> 2;
     const int bh = bp / G.nqb, pos = bp % G.nqb;
     int first = 0;
@@ -802,7 +832,7 @@ __global__ __launch_bounds__(128) void attn_fa_merge_kernel(FaGeom G, const floa
 }
 
 // Geometry of the flash kernel for BH heads of n rows; when there are fewer
-// query blocks than CUs, the split length is chosen so that about 512
+// blocks of 128 queries than CUs, the split length is chosen so that about 512
 // workgroups run.  Returns false when the kernel does not apply.
 bool fa_geom(int dtype, int BH, int n, int dh, int causal, int window, FaGeom& G) {
     if (dtype != kBF16 || dh != 64 || !(n > kAttnLdsMaxN || window > 0)) return false;
@@ -810,7 +840,23 @@ bool fa_geom(int dtype, int BH, int n, int dh, int causal, int window, FaGeom& G
     G.causal = causal;
     G.win = window > 0 && causal;
     G.lb = window > 0 ? window - 1 : n;
-    G.nqb = (n + kFaQB - 1) / kFaQB;
+    // Blocks of 64 queries (QN = 1) where blocks of 128 give a CU at most two
+    // and those of 64 fill the chip.  Causal blocks differ in length: one block
+    // of 128 per CU and the longest sets the time, two of 64 add up to the
+    // average (kernel alone, 32 heads of 1024 rows: 21.1 -> 14.9 us, 64 of 512:
+    // 15.3 -> 10.4; 4 heads of 8192 rows, whole forward: 151 -> 123).  With
+    // more blocks the K and V reads that QN = 2 halves decide (16 heads, B = 32,
+    // T = 1024: 358 us, QN = 1: 399), as with a window, whose blocks are alike
+    // (4 heads of 8192, window 512: 25.5 us, 31.8).  From 256 blocks of 64 on,
+    // one per CU, also up to 2048 rows: shorter than splits and their merge
+    // (8 heads of 2048: 47.5 -> 44.8 us, 4 of 4096: 59.7 -> 62.7); and up to
+    // 512 rows at any number, since so short a block is never split (3 heads
+    // of 500: 30.6 -> 27.0).  Two blocks of 128 per CU: forward of 8 dense heads
+    // of 1024, B = 8, 60.1 -> 51.3 us (QN = 2: 54.4); beside a large MoSA chain
+    // on the other stream (small S = 16 model, B = 16) 0.4% the other way.
+    const long long wg64 = (long long)BH * ((n + 63) / 64), wg128 = (long long)BH * ((n + 127) / 128);
+    G.qn = window == 0 && wg128 <= 512 && (n <= 512 || wg64 >= (n <= 2048 ? 256 : 512)) ? 1 : 2;
+    G.nqb = (n + fa_qb_rows(G) - 1) / fa_qb_rows(G);
     G.tps = 1 << 30;
     long long total = 0;
     int maxt = 0;
@@ -824,7 +870,7 @@ bool fa_geom(int dtype, int BH, int n, int dh, int causal, int window, FaGeom& G
     // merge cost more than the causal imbalance they remove otherwise
     // (measured on 32 heads of 1024 rows: 23.2 us unsplit, 31.2 us with
     // splits of 8 tiles including the merge)
-    if ((long long)BH * G.nqb < 256) {
+    if (G.qn == 2 && wg128 < 256) {
         const long long want = (total * BH + 511) / 512;
         G.tps = (int)(want > 8 ? want : 8);
         if (G.tps >= maxt) G.tps = 1 << 30;
@@ -842,8 +888,10 @@ int launch_attn_fwd_t(const ST* QKV, const float* r, int BH, int n, int dh, int 
     if constexpr (sizeof(ST) == 2) {
         FaGeom G;
         if (fa_geom(kBF16, BH, n, dh, causal, window, G)) {
-            const size_t lds = (size_t)kFaStages * 2 * kFaKB * 64 * 2;
-            auto kern = G.win ? attn_fa_fwd_kernel<true> : attn_fa_fwd_kernel<false>;
+            const size_t lds = (size_t)fa_stages(G.qn) * 2 * kFaKB * 64 * 2;
+            auto kern = G.qn == 1 ? attn_fa_fwd_kernel<false, 1>  // (never with a window)
+                        : G.win   ? attn_fa_fwd_kernel<true, 2>
+                                  : attn_fa_fwd_kernel<false, 2>;
             if (allow_lds((const void*)kern, lds)) return -1;
             const bool split = G.wph > G.nqb;
             if (split && !part) return -1;
@@ -851,7 +899,7 @@ int launch_attn_fwd_t(const ST* QKV, const float* r, int BH, int n, int dh, int 
                                (uint16_t*)A, lse, part);
             if (hipGetLastError() != hipSuccess || mk(dense ? "attn_dense" : "attn")) return -1;
             if (split) {
-                hipLaunchKernelGGL(attn_fa_merge_kernel, dim3(4 * BH * G.nqb), dim3(128), 0, stream, G, part, r,
+                hipLaunchKernelGGL(attn_fa_merge_kernel, dim3(4 * BH * G.nqb), dim3(kFaSplitQB), 0, stream, G, part, r,
                                    (uint16_t*)A, lse);
                 if (hipGetLastError() != hipSuccess || mk(dense ? "attn_dense_merge" : "attn_merge")) return -1;
             }

@@ -69,3 +69,23 @@ def test_f32_tiles(orc, kw):
 ])
 def test_weight_gradient_tiles(orc, kw):
     _check(orc, wl.small(seed=31, **kw))
+
+
+# the flash kernel's blocks of 64 and of 128 queries: short of, at and past a
+# block and a key tile, 256 blocks and more (whole heads per XCD, full and
+# partial rounds of its CUs), more than 512 blocks of 128, a head too short for
+# a second block, MoSA heads
+@pytest.mark.parametrize("kw", [
+    dict(batch=1, seq_len=129, dense_heads=3),
+    dict(batch=1, seq_len=512, dense_heads=1, causal=False),
+    dict(batch=1, seq_len=513, dense_heads=3),
+    dict(batch=8, seq_len=449, dense_heads=8),
+    dict(batch=4, seq_len=520, dense_heads=8),
+    dict(batch=4, seq_len=520, dense_heads=8, causal=False),
+    dict(batch=5, seq_len=1000, dense_heads=8),
+    dict(batch=9, seq_len=1024, dense_heads=8),
+    dict(batch=2, seq_len=400, dense_heads=0, heads=16, k=193),
+])
+def test_flash_blocks(orc, kw):
+    w = wl.small(**{**dict(d_model=64, d_head=64, heads=1, k=4, backward=False, seed=63), **kw})
+    check_forward(orc, w, wl.make_inputs(w))
