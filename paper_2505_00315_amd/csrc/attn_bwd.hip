@@ -16,6 +16,7 @@
 #include "common.h"
 #include "gemm2.h"
 #include "kernels.h"
+#include "launch_parts.h"
 #include "rope.h"
 
 namespace mosa {
@@ -23,15 +24,15 @@ namespace mosa {
 namespace {
 
 // fp32 storage: one workgroup of NW waves per (b, h), pass and block of 16 keys
-// (kv pass, blocks [0, BH nb)) or 16 queries (q pass, the rest).  The waves take
+// (kv pass, even blocks) or 16 queries (q pass, odd blocks).  The waves take
 // the blocks of the other side in turn (wave w the blocks w, w + NW, ...) from
 // global memory and their partial sums are added in wave order through LDS
-// (reproducible).  Such heads are few and short, so the kernel is bound by the
-// latency of its block loop (about 3 us a block) and by how much of the chip
-// it fills: with one wave walking all blocks of its 16 rows, 4 heads of 512
-// rows took 112 us (kv) + 70 us (q) on 32 workgroups per pass; as here both
-// take 21 us on 256 (2 heads of 4096 rows, the whole training step: 1639 ->
-// 531 us).
+// (reproducible).  Bound by the latency of the block loop (about 3 us a block)
+// and, with few or short heads, by how much of the chip they fill: with one
+// wave walking all blocks of its 16 rows, 4 heads of 512 rows took 112 us (kv)
+// + 70 us (q) on 32 workgroups per pass; as here both take 21 us on 256.  The
+// whole training step of 2 heads of 4096 rows: 1639 -> 531 us; of heads that
+// fill the chip either way (16 of 1024 rows, B = 4, d 1024): 2833 -> 1895.
 constexpr int kBwdF32MaxWaves = 8;
 
 template <int DH>
@@ -218,13 +219,14 @@ template <int DH, bool WIN>
 __global__ __launch_bounds__(64 * kBwdF32MaxWaves) void attn_bwd_f32_kernel(
     const float* __restrict__ QKV, const float* __restrict__ dA, const float* __restrict__ lse,
     const float* __restrict__ D, int BH, int n, int causal, int lb, float scale, float* __restrict__ dQKV,
-    const int32_t* __restrict__ rI, const float2* __restrict__ rtab) {
+    const int32_t* __restrict__ rI, const float2* __restrict__ rtab, uint32_t first) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     float4* part = reinterpret_cast<float4*>(smem);
     const int nb = (n + 15) / 16, nw = blockDim.x >> 6;
     // even blocks one pass, odd ones the other, each with the blocks that have
     // the most work first (causal: low keys, high queries)
-    const int b = blockIdx.x, task = b >> 1, bh = task % BH, blk = task / BH;
+    const uint32_t b = first + blockIdx.x;
+    const int task = b >> 1, bh = task % BH, blk = task / BH;
     if (b & 1) {
         attn_bwd_f32_q<DH, WIN>(part, nw, bh, 16 * (causal ? nb - 1 - blk : blk), QKV, dA, lse, D, n, causal, lb, scale,
                                 dQKV, rI, rtab);
@@ -1118,22 +1120,23 @@ int launch_bf16(const uint16_t* QKV, const uint16_t* dA, const float* lse, const
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// fp32 storage: both passes in one launch, up to 8 waves per block of 16 rows
-// (fewer when the head has fewer blocks to share out).
+// fp32 storage: both passes in one launch (launch_parts.h: more than one only
+// past 2^32 threads), up to 8 waves per block of 16 rows.
 int launch_f32(const float* QKV, const float* dA, const float* lse, const float* D, int BH, int n, int dh, int causal,
                int window, float* dQKV, const int32_t* rI, const float2* rtab, hipStream_t stream) {
     if (BH == 0) return 0;
     const float scale = 1.0f / sqrtf((float)dh);
     const int lb = window > 0 ? window - 1 : n, nb = (n + 15) / 16;
-    int nw = 1;
-    while (nw < kBwdF32MaxWaves && 2 * nw <= nb) nw *= 2;
+    const int nw = f32_attn_waves(n, kBwdF32MaxWaves);
     auto kern = window > 0 ? (dh == 64 ? attn_bwd_f32_kernel<64, true> : attn_bwd_f32_kernel<32, true>)
                            : (dh == 64 ? attn_bwd_f32_kernel<64, false> : attn_bwd_f32_kernel<32, false>);
     const size_t lds = dh == 64 ? BwdF32<64>::lds(nw) : BwdF32<32>::lds(nw);
     static_assert(BwdF32<64>::lds(kBwdF32MaxWaves) <= 64 * 1024, "default LDS limit");
-    hipLaunchKernelGGL(kern, dim3(2 * BH * nb), dim3(64 * nw), lds, stream, QKV, dA, lse, D, BH, n, causal, lb, scale,
-                       dQKV, rI, rtab);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    return launch_parts(2 * (uint64_t)BH * nb, 64 * nw, [&](uint32_t first, uint32_t blocks) {
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * nw), lds, stream, QKV, dA, lse, D, BH, n, causal, lb, scale,
+                           dQKV, rI, rtab, first);
+        return hipGetLastError() == hipSuccess ? 0 : -1;
+    });
 }
 
 }  // namespace
