@@ -652,6 +652,12 @@ int run_bwd_proj_t(const uint16_t* X, const uint16_t* dY, const int32_t* I, cons
         RowGemmJob<PX>::lds(0), stream);
 }
 
+// Whether a CU's 160 KB of LDS hold two workgroups of the grouped launch.
+template <class PQ, class PO>
+bool two_per_cu(int rows) {
+    return 2 * std::max(Gemm2Job<PQ>::lds(rows), Gemm2Job<PO>::lds(rows)) <= 160 * 1024;
+}
+
 template <int DH>
 int run_bwd_proj(const uint16_t* X, const uint16_t* dY, const int32_t* I, const uint16_t* A, const uint16_t* dQKV,
                  const uint16_t* dz16, const float* dz, const uint16_t* Wq, const uint16_t* Wk, const uint16_t* Wv,
@@ -660,12 +666,25 @@ int run_bwd_proj(const uint16_t* X, const uint16_t* dY, const int32_t* I, const 
     auto go = [&](auto f) {
         return f(X, dY, I, A, dQKV, dz16, dz, Wq, Wk, Wv, Wr, B, T, d, H, n, dWq, dWk, dWv, dWr, dWo, dXs, stream);
     };
-    // 128-column tiles where they still give every CU one
+    using PQN = WgradQkvPolicy2<DH, 64>;
+    using PON = WgradOPolicy2<DH, 64>;
     if constexpr (DH == 64) {
-        if (d % 128 == 0 && H * (d / 128) >= kFullChip)
-            return go(run_bwd_proj_t<WgradQkvPolicy2<DH, 128>, WgradOPolicy2<DH, 128>, DH>);
+        using PQW = WgradQkvPolicy2<DH, 128>;
+        using POW = WgradOPolicy2<DH, 128>;
+        // 128-column tiles where they still give every CU one, unless their
+        // rings and row tables (with R rows) let a CU hold one workgroup where
+        // those of 64 columns let it hold two: up to 1024 rows two of either,
+        // up to 2048 two of 64 columns only, beyond one of either.  Training
+        // step with 64 columns against 128, T = 256, k = 64 (us): 27 heads of
+        // d 1280, R = 512 124 against 117, 1024 198 / 189, 1536 260 / 273,
+        // 2048 331 / 346, 3072 532 / 491; 128 heads of d 1024, 1024 563 / 533,
+        // 1536 859 / 890, 2048 1144 / 1182, 3072 1911 / 1713.
+        const int rows = (B * n + 63) / 64 * 64;
+        if (d % 128 == 0 && H * (d / 128) >= kFullChip &&
+            (two_per_cu<PQW, POW>(rows) || !two_per_cu<PQN, PON>(rows)))
+            return go(run_bwd_proj_t<PQW, POW, DH>);
     }
-    return go(run_bwd_proj_t<WgradQkvPolicy2<DH, 64>, WgradOPolicy2<DH, 64>, DH>);
+    return go(run_bwd_proj_t<PQN, PON, DH>);
 }
 
 // Bytes of fp32 partial sums the two launches of one head group need.

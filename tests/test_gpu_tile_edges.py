@@ -57,13 +57,16 @@ def test_f32_tiles(orc, kw):
 
 # the weight gradients' row tables and tiles: rows per head short of, at and
 # past a chunk of 32 or 64, one to many chunks and tiles per workgroup, the
-# 64- and the 128-column tiles (128 heads of d 256), dense row ranges
+# 64- and the 128-column tiles (128 heads of d 256; with 1250 rows, 64 columns
+# again, with 2100, 128), dense row ranges
 @pytest.mark.parametrize("kw", [
     dict(batch=1, seq_len=150, k=133, heads=2, d_model=192, d_head=64),
     dict(batch=3, seq_len=90, k=64, heads=3, d_model=320, d_head=64),
     dict(batch=2, seq_len=150, k=65, heads=5, d_model=128, d_head=32),
     dict(batch=1, seq_len=160, k=160, heads=128, d_model=256, d_head=64),
     dict(batch=2, seq_len=100, k=67, heads=130, d_model=256, d_head=64),
+    dict(batch=5, seq_len=260, k=250, heads=128, d_model=256, d_head=64),
+    dict(batch=7, seq_len=310, k=300, heads=128, d_model=256, d_head=64),
     dict(batch=1, seq_len=33, k=5, heads=1, dense_heads=3, d_model=128, d_head=64),
     dict(batch=3, seq_len=171, k=5, heads=1, dense_heads=2, d_model=64, d_head=32),
 ])
