@@ -40,7 +40,7 @@ struct BwdOutPolicy {
         ST* dA;
         float* D;
         float* dz;         // nullptr: dense head
-        ST* dz16;          // [B, H, n, 16]
+        ST* dz16;          // [B, H, n, 16], or nullptr where nothing reads it
         int T, d, H, n, M, mtiles;
     };
     struct ARef {
@@ -122,9 +122,11 @@ struct BwdOutPolicy {
             if (a.dz) {
                 const float dzv = part * (1.f - rr);
                 a.dz[ri] = dzv;
-                float x[8] = {dzv, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, zz[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                vec8_store<ST>(a.dz16 + ri * 16, vec8_from_f32<ST>(x));
-                vec8_store<ST>(a.dz16 + ri * 16 + 8, vec8_from_f32<ST>(zz));
+                if (a.dz16) {
+                    const float x[8] = {dzv, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                    vec8_store<ST>(a.dz16 + ri * 16, vec8_from_f32<ST>(x));
+                    vec8_store<ST>(a.dz16 + ri * 16 + 8, vec8_zero<ST>());
+                }
             }
         }
     }

@@ -492,7 +492,7 @@ int launch_bwd_head(int dtype, const void* X, const void* dY, const int32_t* I, 
     const long long R = (long long)B * k;
     // up to 128 rows (measured: 86 us instead of 125 us for 256 heads of 128
     // rows; at 256 rows the grouped tile kernel is faster, 84 us instead of 93)
-    if (dtype != kBF16 || dh != kBhDH || H == 0 || !I || R > 128 || d % 64 != 0 || d > 16384) return 1;
+    if (dtype != kBF16 || dh != kBhDH || H == 0 || !I || R > kBwdHeadMaxRows || d % 64 != 0 || d > 16384) return 1;
     // buffer-store ranges (32-bit byte offsets)
     if ((long long)H * d * kBhDH * 2 >= (1ll << 31) || R * H * d * 2 >= (1ll << 31)) return 1;
     using ST = uint16_t;

@@ -22,6 +22,7 @@ struct Layout {
     size_t z, xnorm, unc_tok, unc_key, unc_sel, Xo, ybase, apart, apart_d;
     // backward scratch
     size_t dA, D, dz, dz16, dQKV, dXs, dAd, Dd, dQKVd, wpart, wpart_d, dxbase, dwr;
+    size_t dz16_bytes;
     size_t fwd_scratch, scratch_total;
 };
 
@@ -105,7 +106,11 @@ Layout make_layout(const mosa_shape* s) {
     L.dA = bw.take(B * H * k * dh * es);
     L.D = bw.take(B * H * k * 4);
     L.dz = bw.take(B * H * k * 4);
-    L.dz16 = bw.take(B * H * k * 16 * es);
+    L.dz16_bytes = H > 0 && wgrad_reads_dz16(s->dtype == MOSA_BF16 ? kBF16 : kF32, (int)B, (int)T, (int)d, (int)H,
+                                             (int)dh, (int)k)
+                       ? B * H * k * 16 * es
+                       : 0;
+    L.dz16 = bw.take(L.dz16_bytes);
     L.dQKV = bw.take(B * H * k * 3 * dh * es);
     L.dXs = bw.take(B * H * k * d * es);
     L.dAd = bw.take(B * Hd * T * dh * es);
@@ -425,7 +430,7 @@ int mosa_backward_timed(const mosa_shape* s, const void* X, const mosa_weights* 
     void* dA = at<char>(scratch, L.dA);
     float* D = at<float>(scratch, L.D);
     float* dz = at<float>(scratch, L.dz);
-    void* dz16 = at<char>(scratch, L.dz16);
+    void* dz16 = L.dz16_bytes ? at<char>(scratch, L.dz16) : nullptr;
     void* dQKV = at<char>(scratch, L.dQKV);
     void* dXs = at<char>(scratch, L.dXs);
     void* dAd = at<char>(scratch, L.dAd);

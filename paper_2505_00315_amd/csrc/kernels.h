@@ -87,7 +87,7 @@ bool combine_split_ok(int d, int H);
 
 // Backward, output side of a head (A is the r-scaled attention output):
 // dA~ = dY[I] Wo^T; dA = r dA~; D = <dA~, A>; dz = D (1 - r) (also as 16-wide
-// rows dz16); dz, dz16 may be null and I, r null for dense heads.
+// rows dz16 unless that is null); dz, dz16, I and r are null for dense heads.
 int launch_dattn_out(int dtype, const void* dY, const int32_t* I, const float* r, const void* Wo,
                      const void* A, int B, int T, int d, int H, int dh, int n, void* dA, float* D, float* dz,
                      void* dz16, hipStream_t stream);
@@ -109,6 +109,10 @@ int launch_wgrad(int dtype, const void* X, const void* dY, const int32_t* I, con
                  void* dWq, void* dWk, void* dWv, void* dWr, void* dWo, float* part, int which, const Marker& mk,
                  hipStream_t stream);
 size_t wgrad_partial_bytes(int dtype, int B, int T, int d, int H, int dh, int n, int router);
+// Whether the weight gradients of these MoSA heads read the 16-wide rows dz16
+// (launch_bwd_proj or launch_wgrad); otherwise dz16 may be null.
+bool wgrad_reads_dz16(int dtype, int B, int T, int d, int H, int dh, int n);
+constexpr int kBwdHeadMaxRows = 128;  // most rows per head of launch_bwd_head
 // The MoSA heads' dW^{Q,K,V,r}, dW^O and per-head dX rows (launch_dx_proj) in
 // one grouped launch; returns 1, launching nothing, where that does not apply.
 int launch_bwd_proj(int dtype, const void* X, const void* dY, const int32_t* I, const void* A, const void* dQKV,

@@ -41,7 +41,7 @@ struct WgradQkvPolicy {
         const ST* X;
         const int32_t* I;
         const ST* dQKV;  // [B, H, n, 3*DH]
-        const ST* dz16;  // [B, H, n, 16]
+        const ST* dz16;  // [B, H, n, 16] (the engine of gemm.h)
         ST* dWq;
         ST* dWk;
         ST* dWv;         // [H, d, DH]
@@ -49,7 +49,7 @@ struct WgradQkvPolicy {
         float* part;     // [S, H, d, NT] fp32 partial sums (S > 1)
         int T, d, H, n, R, mtiles, S, cps;
         FastDiv nd;
-        const float* dz; // [B, H, n] (the wide tiles)
+        const float* dz; // [B, H, n] (the gathered-row engine)
     };
     struct ARef {};
     struct BRef {};
@@ -769,6 +769,15 @@ int launch_bwd_proj(int dtype, const void* X, const void* dY, const int32_t* I, 
     return f((const ST*)X, (const ST*)dY, I, (const ST*)A, (const ST*)dQKV, (const ST*)dz16, dz, (const ST*)Wq,
              (const ST*)Wk, (const ST*)Wv, (const ST*)Wr, B, T, d, H, n, (ST*)dWq, (ST*)dWk, (ST*)dWv, (ST*)dWr,
              (ST*)dWo, (ST*)dXs, stream);
+}
+
+// The gathered-row engine takes dz in fp32; the per-head kernel of few rows and
+// the engine of gemm.h take the 16-wide rows.
+bool wgrad_reads_dz16(int dtype, int B, int T, int d, int H, int dh, int n) {
+    const long long R = (long long)B * n;
+    if (dtype != kBF16 || (dh == 64 && R <= kBwdHeadMaxRows)) return true;
+    return !(dh == 64 ? wgrad2_table_rows<WgradQkvPolicy2<64, 64>>((int)R, d, (long long)B * T, R * H, 64)
+                      : wgrad2_table_rows<WgradQkvPolicy2<32, 64>>((int)R, d, (long long)B * T, R * H, 32));
 }
 
 size_t wgrad_partial_bytes(int dtype, int B, int T, int d, int H, int dh, int n, int router) {

@@ -46,6 +46,21 @@ def test_workspace_size_and_layout():
         assert v % 256 == 0
 
 
+@pytest.mark.parametrize("batch,k,heads,dz16", [(4, 256, 128, False), (1, 128, 256, True), (1, 129, 256, False),
+                                                  (16, 256, 32, False), (17, 256, 32, True)])
+def test_backward_scratch_without_unread_rows(batch, k, heads, dz16):
+    """Pure bf16 layer with k = T: the backward's scratch is dA, D, dz, dQ | dK | dV and the dX rows (no weight-gradient
+    partials up to 4096 rows per head), and the 16-wide copy of dz only where a kernel reads it: up to 128 rows per
+    head, or past the 4096 of the row tables."""
+    d, dh = 64, 64
+    s = mosa.make_shape(batch, k, d, heads, dh, k, True, 0, "bf16")
+    rows = batch * heads * k
+    parts = [rows * dh * 2, rows * 4, rows * 4, rows * 3 * dh * 2, rows * d * 2] + ([rows * 32] if dz16 else [])
+    want = sum(-(-p // 256) * 256 for p in parts)
+    got = mosa.workspace_size(s)[1]
+    assert got == want if batch * k <= 4096 else got >= want
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(k=0), mosa.MOSA_ERR_INVALID_ARG),
     (dict(k=1025), mosa.MOSA_ERR_INVALID_ARG),
