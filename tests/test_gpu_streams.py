@@ -1,10 +1,12 @@
 """The layer on caller streams other than the default one, and from several
 host threads at once.  The untimed calls of a layer with both kinds of heads
 run the dense heads' kernels on the library's auxiliary stream, forked from
-and joined back into the caller's stream inside each call: results must be
-bitwise the same whatever stream the caller uses, for back-to-back calls
-without a host synchronisation between them, and for calls that two host
-threads enqueue at the same time on two streams."""
+and joined back into the caller's stream inside each call, where there is
+enough work in them ("f32" and "bf16_large"; "bf16_small" stays on one stream):
+results must be bitwise the same whatever stream the caller uses, for
+back-to-back calls without a host synchronisation between them, and for calls
+that two host threads enqueue at the same time on two streams."""
+import dataclasses
 import threading
 
 import numpy as np
@@ -17,7 +19,13 @@ from paper_2505_00315_amd import mosa
 
 pytestmark = pytest.mark.gpu
 
-W = wl.small(name="streams_hybrid", batch=2, seq_len=256, heads=4, k=16, d_head=64, d_model=128, dense_heads=2)
+SMALL = dict(batch=2, seq_len=256, heads=4, k=16, d_head=64, d_model=128, dense_heads=2)
+CASES = {
+    "bf16_small": wl.small(name="streams_hybrid", **SMALL),
+    "f32": wl.small(name="streams_hybrid_f32", dtype="f32", **SMALL),
+    "bf16_large": wl.small(name="streams_hybrid_large", batch=3, seq_len=1024, d_model=1024, heads=8, d_head=64, k=32,
+                           dense_heads=4),
+}
 
 
 def _alloc(dev):
@@ -25,9 +33,9 @@ def _alloc(dev):
     return grads
 
 
-def _step(dev, stream=None):
+def _step(w, dev, stream=None):
     """Forward and backward on `stream` (None: the current stream), no host sync."""
-    shape = shape_of(W)
+    shape = shape_of(w)
     weights = {n: dev.get(n) for n in mosa.WEIGHT_NAMES}
     Y, saved, scratch = mosa.forward(shape, dev["X"], weights, stream=stream)
     grads = _alloc(dev)
@@ -45,35 +53,34 @@ def _same(a, b, what):
         assert np.array_equal(a[k], b[k]), f"{what}: {k} differs"
 
 
-@pytest.fixture(scope="module")
-def reference():
-    inp = wl.make_inputs(W, with_grad=True)
-    dev = device_inputs(inp)
-    out = _step(dev)
+@pytest.fixture(scope="module", params=list(CASES))
+def reference(request):
+    w = CASES[request.param]
+    dev = device_inputs(wl.make_inputs(w, with_grad=True))
+    out = _step(w, dev)
     torch.cuda.synchronize()
-    mosa.check_selection(shape_of(W), out["saved"])
-    return dev, _host(out)
+    mosa.check_selection(shape_of(w), out["saved"])
+    return w, dev, _host(out)
 
 
 def test_side_stream_matches_default(reference):
-    dev, ref = reference
+    w, dev, ref = reference
     s = torch.cuda.Stream()
     s.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(s):
-        out = _step(dev, stream=s)
+        out = _step(w, dev, stream=s)
     s.synchronize()
     _same(_host(out), ref, "side stream")
 
 
 def test_back_to_back_calls(reference):
-    dev, ref = reference
+    w, dev, ref = reference
     # two different inputs enqueued back to back, then the reference input
     # again, with no host synchronisation in between
-    other = device_inputs(wl.make_inputs(wl.small(name="streams_other", batch=2, seq_len=256, heads=4, k=16,
-                                                  d_head=64, d_model=128, dense_heads=2, seed=9), with_grad=True))
-    out_a = _step(dev)
-    out_b = _step(other)
-    out_c = _step(dev)
+    other = device_inputs(wl.make_inputs(dataclasses.replace(w, seed=w.seed + 9), with_grad=True))
+    out_a = _step(w, dev)
+    out_b = _step(w, other)
+    out_c = _step(w, dev)
     torch.cuda.synchronize()
     _same(_host(out_a), ref, "first call")
     _same(_host(out_c), ref, "third call")
@@ -81,7 +88,7 @@ def test_back_to_back_calls(reference):
 
 
 def test_two_host_threads(reference):
-    dev, ref = reference
+    w, dev, ref = reference
     results, errors = {}, []
 
     def worker(tid):
@@ -89,7 +96,7 @@ def test_two_host_threads(reference):
             torch.cuda.set_device(0)
             s = torch.cuda.Stream()
             with torch.cuda.stream(s):
-                outs = [_step(dev, stream=s) for _ in range(3)]
+                outs = [_step(w, dev, stream=s) for _ in range(3)]
             s.synchronize()
             results[tid] = [_host(o) for o in outs]
         except Exception as exc:  # reported by the main thread

@@ -1,8 +1,10 @@
-"""Layers whose dense heads are large enough to run on the library's auxiliary
-stream (bf16: 6 GFLOP of dense forward; fp32: any), and layers just below that
-size, which stay on the caller's stream: the results equal those of the
-stage-timed calls (one stream, one serial order) bit for bit, for back-to-back
-calls and for calls that two host threads enqueue at the same time."""
+"""Layers with enough work for the library's auxiliary stream (bf16: 6 GFLOP of
+forward, the dense heads' plus twice the MoSA heads'; fp32: any), and layers just
+below that size, which stay on the caller's stream: the results equal those of
+the stage-timed calls (one stream, one serial order) bit for bit, for
+back-to-back calls, for calls that two host threads enqueue at the same time,
+and for calls on different inputs that share one saved and one scratch buffer."""
+import dataclasses
 import threading
 
 import pytest
@@ -73,3 +75,40 @@ def test_same_as_one_serial_order(name):
     for t, outs in got.items():
         for i, o in enumerate(outs):
             _same(o, ref, f"thread {t} call {i}")
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_shared_buffers(name):
+    """A program keeps one saved and one scratch buffer: the calls of a pass
+    rewrite what the previous pass's kernels on either stream read.  Passes on
+    two different inputs in turn, enqueued without waiting, forward and
+    backward together and forwards alone, equal the one-stream calls."""
+    w = CASES[name]
+    print(f"\n[case] {w}", flush=True)
+    shape = shape_of(w)
+    devs = [device_inputs(wl.make_inputs(dataclasses.replace(w, seed=w.seed + i), with_grad=True)) for i in range(2)]
+    weights = [{n: dev.get(n) for n in mosa.WEIGHT_NAMES} for dev in devs]
+    timer = mosa.StageTimer(sets=2)
+    refs = []
+    for dev in devs:
+        refs.append(_step(w, dev, timer=timer)[0])
+        torch.cuda.synchronize()
+    timer.close()
+    assert not torch.equal(refs[0]["Y"], refs[1]["Y"])
+    saved, scratch = mosa.alloc_workspace(shape)
+    # every pass has outputs of its own, allocated (and poisoned) beforehand
+    passes = [0, 1, 0, 1, 1, 0]
+    outs = [{n: torch.full_like(t, float("nan")) for n, t in refs[i].items()} for i in passes]
+    ys = [torch.full_like(refs[i]["Y"], float("nan")) for i in passes]
+    torch.cuda.synchronize()
+    for i, o in zip(passes, outs):
+        dev = devs[i]
+        mosa.forward(shape, dev["X"], weights[i], Y=o["Y"], saved=saved, scratch=scratch)
+        mosa.backward(shape, dev["X"], weights[i], dev["dY"], saved, {n: t for n, t in o.items() if n.startswith("dW")},
+                      dX=o["dX"], scratch=scratch)
+    for i, y in zip(passes, ys):
+        mosa.forward(shape, devs[i]["X"], weights[i], Y=y, saved=saved, scratch=scratch)
+    torch.cuda.synchronize()
+    for n, (i, o, y) in enumerate(zip(passes, outs, ys)):
+        _same(o, refs[i], f"pass {n}")
+        _same({"Y": y}, {"Y": refs[i]["Y"]}, f"forward {n}")
