@@ -40,7 +40,8 @@ def test_row_tiles(orc, batch, k, rope, causal):
 
 
 # fp32: the small tiles (few workgroups) and the large ones (64 heads of 260
-# rows), rows and blocks of 16 short of, at and past their edges, 1 to 8 waves
+# rows for the forward and the rows' products, the last two cases for the
+# others), rows and blocks of 16 short of, at and past their edges, 1 to 8 waves
 # sharing a block's loop, dense heads with and without a window
 @pytest.mark.parametrize("kw", [
     dict(seq_len=15, k=7, heads=1, dense_heads=1, d_head=64),
@@ -50,15 +51,19 @@ def test_row_tiles(orc, batch, k, rope, causal):
     dict(seq_len=150, k=130, heads=64, dense_heads=0, d_head=32, batch=2),
     dict(seq_len=150, k=130, heads=64, dense_heads=0, d_head=64, batch=2, rope=True),
     dict(seq_len=300, k=3, heads=1, dense_heads=9, d_model=256, d_head=64, window=100),
+    # the large tiles of the weight gradients with the router column (256 heads of one tile) and of the dense heads
+    dict(seq_len=45, k=20, heads=256, dense_heads=0, d_model=64, d_head=64, batch=2),
+    dict(seq_len=1030, k=3, heads=1, dense_heads=4, d_model=512, d_head=64, batch=4),
 ])
 def test_f32_tiles(orc, kw):
     _check(orc, wl.small(dtype="f32", seed=77, **kw))
 
 
 # the weight gradients' row tables and tiles: rows per head short of, at and
-# past a chunk of 32 or 64, one to many chunks and tiles per workgroup, the
-# 64- and the 128-column tiles (128 heads of d 256; with 1250 rows, 64 columns
-# again, with 2100, 128), dense row ranges
+# past a chunk of 32 or 64, one to many chunks, the 64- and the 128-column tiles
+# (128 heads of d 256; with 1250 rows, 64 columns again, with 2100, 128), two and
+# three tiles per workgroup of 1, 2, 3 or 5 chunks with a shorter last
+# workgroup (from 208 heads on), dense row ranges
 @pytest.mark.parametrize("kw", [
     dict(batch=1, seq_len=150, k=133, heads=2, d_model=192, d_head=64),
     dict(batch=3, seq_len=90, k=64, heads=3, d_model=320, d_head=64),
@@ -67,6 +72,11 @@ def test_f32_tiles(orc, kw):
     dict(batch=2, seq_len=100, k=67, heads=130, d_model=256, d_head=64),
     dict(batch=5, seq_len=260, k=250, heads=128, d_model=256, d_head=64),
     dict(batch=7, seq_len=310, k=300, heads=128, d_model=256, d_head=64),
+    dict(batch=1, seq_len=50, k=20, heads=208, d_model=320, d_head=32),
+    dict(batch=1, seq_len=120, k=97, heads=208, d_model=320, d_head=32),
+    dict(batch=1, seq_len=170, k=161, heads=208, d_model=320, d_head=32),
+    dict(batch=1, seq_len=60, k=33, heads=256, d_model=448, d_head=32),
+    dict(batch=1, seq_len=140, k=133, heads=256, d_model=640, d_head=64),
     dict(batch=1, seq_len=33, k=5, heads=1, dense_heads=3, d_model=128, d_head=64),
     dict(batch=3, seq_len=171, k=5, heads=1, dense_heads=2, d_model=64, d_head=32),
 ])
