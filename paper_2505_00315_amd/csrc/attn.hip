@@ -615,7 +615,6 @@ __global__ __launch_bounds__(256) void attn_fa_fwd_kernel(const uint16_t* __rest
         __syncthreads();              // for every wave; the buffer of tile it - 1 is free
         issue(it + STG - 1, (BUF + STG - 1) % STG);
         const unsigned char* Kb = smem + BUF * STAGE;
-        const unsigned char* Vb = Kb + TILE;
         const int j0 = lo + KB * (tbeg + it);
 
         // Every LDS read of the tile first (the V^T fragments are needed only

@@ -457,13 +457,8 @@ __device__ __forceinline__ void attn_bwd_kv_tiled_body(unsigned char* smem, int 
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int e = (16 * cb + c16) * LDR + db * 16 + 4 * g + i;
-                if constexpr (sizeof(ST) == 2) {
-                    Ks_out[e] = f32_to_bf16(dKt[cb][db][i] * scale);
-                    Vs_out[e] = f32_to_bf16(dVt[cb][db][i]);
-                } else {
-                    Ks_out[e] = dKt[cb][db][i] * scale;
-                    Vs_out[e] = dVt[cb][db][i];
-                }
+                Ks_out[e] = f32_to_bf16(dKt[cb][db][i] * scale);
+                Vs_out[e] = f32_to_bf16(dVt[cb][db][i]);
             }
     __syncthreads();
 #pragma unroll
@@ -643,8 +638,7 @@ __device__ __forceinline__ void attn_bwd_q_tiled_body(unsigned char* smem, int b
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int e = (16 * cb + c16) * LDR + db * 16 + 4 * g + i;
-                if constexpr (sizeof(ST) == 2) Qs_out[e] = f32_to_bf16(dQt[cb][db][i] * scale);
-                else Qs_out[e] = dQt[cb][db][i] * scale;
+                Qs_out[e] = f32_to_bf16(dQt[cb][db][i] * scale);
             }
     __syncthreads();
 #pragma unroll

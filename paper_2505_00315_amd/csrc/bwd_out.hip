@@ -30,7 +30,7 @@ struct BwdOutPolicy {
     static constexpr int MT = !SMALL ? 64 : DH == 64 ? 16 : 32, NT = DH, KC = sizeof(ST) == 2 ? 64 : 32;
     static constexpr int WM = MT == 64 ? 4 : MT / 16, WN = 4 / WM;
     static constexpr size_t EPI_LDS = 0;
-    static constexpr bool A_KCONTIG = true, B_KCONTIG = true, A_SCALED = false;
+    static constexpr bool A_KCONTIG = true, B_KCONTIG = true;
     struct Args {
         const ST* dY;
         const int32_t* I;  // nullptr: dense head
@@ -65,7 +65,7 @@ struct BwdOutPolicy {
         n0 = 0;
     }
     __device__ static int k_size(const Args& a, int) { return a.d; }
-    __device__ static ARef a_row(const Args& a, int h, int m, float&) {
+    __device__ static ARef a_row(const Args& a, int h, int m) {
         if (m < 0 || m >= a.M) return {nullptr};
         const int b = m / a.n, i = m % a.n;
         const int t = a.I ? a.I[((size_t)b * a.H + h) * a.n + i] : i;
@@ -79,7 +79,6 @@ struct BwdOutPolicy {
     __device__ static RowInfo row_info(const Args&, int, int) { return {0}; }
     __device__ static const ST* a_kaddr(const Args& a, int, const RowInfo&, int) { return a_fallback(a); }
     __device__ static bool a_kok(const Args&, int, const RowInfo&, int) { return false; }
-    __device__ static float a_kscale(const Args&, int, const RowInfo&) { return 1.f; }
     __device__ static const ST* b_kaddr(const Args& a, int, const RowInfo&, int) { return b_fallback(a); }
     __device__ static bool b_kok(const Args&, int, const RowInfo&, int) { return false; }
 
@@ -147,8 +146,7 @@ struct BwdOutPolicy2 {
     __device__ static void tile(const Args& a, int logical, int& h, int& m0, int& n0) { P1::tile(a, logical, h, m0, n0); }
     __device__ static int k_size(const Args& a, int) { return a.d; }
     __device__ static ARef a_row(const Args& a, int h, int m) {
-        float unused;
-        return P1::a_row(a, h, min(m, a.M - 1), unused);
+        return P1::a_row(a, h, min(m, a.M - 1));
     }
     __device__ static const ST* a_elem(const Args&, int, const ARef& r, int k) { return r.p + k; }
     __device__ static BRef b_row(const Args& a, int h, int n) { return {a.Wo + ((size_t)h * DH + n) * a.d}; }

@@ -26,7 +26,7 @@ template <typename ST, int DH, bool SMALL = false>
 struct DxProjPolicy {
     static constexpr int MT = SMALL ? 32 : 64, NT = SMALL ? 64 : 128, KC = (sizeof(ST) == 2 && DH == 64) ? 64 : 32, WM = 2, WN = 2;
     static constexpr size_t EPI_LDS = 0;
-    static constexpr bool A_KCONTIG = true, B_KCONTIG = true, A_SCALED = false;
+    static constexpr bool A_KCONTIG = true, B_KCONTIG = true;
     struct Args {
         const ST* dQKV;  // [B, H, k, 3*DH]
         const float* dz; // [B, H, k]
@@ -59,7 +59,7 @@ struct DxProjPolicy {
     __device__ static size_t ridx(const Args& a, int h, int m) {
         return ((size_t)(m / a.k) * a.H + h) * a.k + (m % a.k);
     }
-    __device__ static ARef a_row(const Args& a, int h, int m, float&) {
+    __device__ static ARef a_row(const Args& a, int h, int m) {
         if (m < 0 || m >= a.M) return {nullptr};
         return {a.dQKV + ridx(a, h, m) * (3 * DH)};
     }
@@ -74,7 +74,6 @@ struct DxProjPolicy {
     __device__ static RowInfo row_info(const Args&, int, int) { return {0}; }
     __device__ static const ST* a_kaddr(const Args& a, int, const RowInfo&, int) { return a_fallback(a); }
     __device__ static bool a_kok(const Args&, int, const RowInfo&, int) { return false; }
-    __device__ static float a_kscale(const Args&, int, const RowInfo&) { return 1.f; }
     __device__ static const ST* b_kaddr(const Args& a, int, const RowInfo&, int) { return b_fallback(a); }
     __device__ static bool b_kok(const Args&, int, const RowInfo&, int) { return false; }
     __device__ static void epilogue(const Args& a, int h, int m0, int n0, const float* Cs, int ldc, int tid, unsigned char*) {
@@ -98,7 +97,7 @@ template <typename ST, int DH, bool SMALL = false>
 struct DxCombinePolicy {
     static constexpr int MT = SMALL ? 32 : 64, NT = SMALL ? 64 : 128, KC = 32, WM = 2, WN = 2;
     static constexpr size_t EPI_LDS = kCombineLds;
-    static constexpr bool A_KCONTIG = true, B_KCONTIG = true, A_SCALED = false;
+    static constexpr bool A_KCONTIG = true, B_KCONTIG = true;
     struct Args {
         const ST* dQKVd;      // [B, Hd, T, 3*DH]
         const ST* Wq;
@@ -128,7 +127,7 @@ struct DxCombinePolicy {
         n0 = (rem % a.ntiles) * NT;
     }
     __device__ static int k_size(const Args& a, int) { return a.Hd * 3 * DH; }
-    __device__ static ARef a_row(const Args& a, int b, int t, float&) {
+    __device__ static ARef a_row(const Args& a, int b, int t) {
         if (t < 0 || t >= a.T) return {nullptr};
         return {a.dQKVd + ((size_t)b * a.Hd * a.T + t) * (3 * DH)};
     }
@@ -146,11 +145,11 @@ struct DxCombinePolicy {
     __device__ static RowInfo row_info(const Args&, int, int) { return {0}; }
     __device__ static const ST* a_kaddr(const Args& a, int, const RowInfo&, int) { return a_fallback(a); }
     __device__ static bool a_kok(const Args&, int, const RowInfo&, int) { return false; }
-    __device__ static float a_kscale(const Args&, int, const RowInfo&) { return 1.f; }
     __device__ static const ST* b_kaddr(const Args& a, int, const RowInfo&, int) { return b_fallback(a); }
     __device__ static bool b_kok(const Args&, int, const RowInfo&, int) { return false; }
     __device__ static void epilogue(const Args& a, int b, int m0, int n0, const float* Cs, int ldc, int tid,
                                     unsigned char* extra) {
+        static_assert(MT == 64 && NT == 128, "combine_tile covers a 64 x 128 tile");
         combine_tile<ST>(Cs, ldc, tid, b, m0, n0, a.T, a.d, a.H, a.k, a.slot, a.dXs, a.dX, a.accumulate,
                          reinterpret_cast<int16_t*>(extra));
     }

@@ -12,7 +12,7 @@
 //                P::B_KCONTIG with BRef / b_row / b_elem;
 //   otherwise    the source is m- (or n-) contiguous: "row" k of the operand
 //                is described by P::RowInfo = P::row_info(k) (e.g. a gathered
-//                token row and a router value), computed one chunk ahead into
+//                token row), computed one chunk ahead into
 //                LDS so that the data loads of a chunk depend on LDS only;
 //                a_kaddr(info, m8) / b_kaddr(info, n8) give an address of 8
 //                consecutive elements that is always safe to load (clamped),
@@ -25,8 +25,7 @@
 // a_fallback / b_fallback give a valid address that is loaded (and then
 // zeroed) in place of out-of-range k-contiguous vectors, so that every load of
 // a chunk is issued without a branch and waited for only at the commit.
-// Rows may be gathered (token indices), scaled (router values) or come from
-// concatenated matrices; out-of-range vectors are nullptr and read as zero.
+// Rows may be gathered (token indices) or come from concatenated matrices; out-of-range vectors are nullptr and read as zero.
 // The K loop is double-buffered: the global loads of chunk c+1 are issued
 // before the MFMAs of chunk c.  After the loop the fp32 C tile is written to
 // LDS (reusing the operand buffers) and P::epilogue writes it out with wide,
@@ -93,14 +92,6 @@ template <> __device__ __forceinline__ Vec8<float> vec8_from_f32<float>(const fl
     return {make_float4(x[0], x[1], x[2], x[3]), make_float4(x[4], x[5], x[6], x[7])};
 }
 
-template <typename ST> __device__ __forceinline__ Vec8<ST> vec8_scale(const Vec8<ST>& v, float s) {
-    float x[8];
-    vec8_to_f32<ST>(v, x);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) x[j] *= s;
-    return vec8_from_f32<ST>(x);
-}
-
 // out[j] holds element j of every in[i] (an 8 x 8 transpose).
 __device__ __forceinline__ void transpose8(const Vec8<uint16_t> (&in)[8], Vec8<uint16_t> (&out)[8]) {
     uint32_t w[8][4];
@@ -120,19 +111,6 @@ __device__ __forceinline__ void transpose8(const Vec8<uint16_t> (&in)[8], Vec8<u
         out[j].v = make_uint4(o[0], o[1], o[2], o[3]);
     }
 }
-__device__ __forceinline__ void transpose8(const Vec8<float> (&in)[8], Vec8<float> (&out)[8]) {
-    float x[8][8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) vec8_to_f32<float>(in[i], x[i]);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        float y[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) y[i] = x[i][j];
-        out[j] = vec8_from_f32<float>(y);
-    }
-}
-
 template <class P>
 struct GemmShape {
     static constexpr int MT = P::MT, NT = P::NT, KC = P::KC, WM = P::WM, WN = P::WN;
@@ -169,16 +147,15 @@ struct GemmShape {
     }
 };
 
-// Staging registers for one operand tile (raw loads plus validity and scale;
-// masking and scaling are applied when the tile is committed to LDS).
+// Staging registers for one operand tile (raw loads plus validity; masking is
+// applied when the tile is committed to LDS).
 template <typename ST, bool KCONTIG, int PER> struct Stage;
 template <typename ST, int PER> struct Stage<ST, true, PER> {
     Vec8<ST> v[PER];
     bool ok[PER];
 };
-template <typename ST, int PER> struct Stage<ST, false, PER> {
-    Vec8<ST> v[PER][8];
-    float sc[PER][8];
+template <int PER> struct Stage<uint16_t, false, PER> {
+    Vec8<uint16_t> v[PER][8];
     uint32_t ok[PER];  // bit i: row i of the 8 x 8 block is valid
 };
 
@@ -233,14 +210,12 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
 
     // Per-thread row references of the k-contiguous operands (fixed across chunks).
     typename P::ARef arow[S::A_PER > 0 ? S::A_PER : 1];
-    float ascale[S::A_PER > 0 ? S::A_PER : 1];
     typename P::BRef brow[S::B_PER > 0 ? S::B_PER : 1];
     if constexpr (P::A_KCONTIG) {
 #pragma unroll
         for (int j = 0; j < S::A_PER; ++j) {
             const int v = tid + 256 * j;
-            ascale[j] = 1.f;
-            arow[j] = P::a_row(args, batch, v < S::A_VECS ? m0 + v / (KC / 8) : -1, ascale[j]);
+            arow[j] = P::a_row(args, batch, v < S::A_VECS ? m0 + v / (KC / 8) : -1);
         }
     }
     if constexpr (P::B_KCONTIG) {
@@ -310,7 +285,6 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         ok |= (uint32_t)P::a_kok(args, batch, ri[i], m8) << i;
-                        sa.sc[j][i] = P::a_kscale(args, batch, ri[i]);
                         sa.v[j][i] = vec8_load<ST>(P::a_kaddr(args, batch, ri[i], m8));
                     }
                     sa.ok[j] = ok;
@@ -367,11 +341,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
 #pragma unroll
             for (int j = 0; j < S::A_PER; ++j) {
                 const int v = tid + 256 * j;
-                if (v < S::A_VECS) {
-                    Vec8<ST> x = sa.ok[j] ? sa.v[j] : vec8_zero<ST>();
-                    if (P::A_SCALED) x = vec8_scale<ST>(x, ascale[j]);
-                    vec8_store<ST>(a + (v / (KC / 8)) * LDK + (v % (KC / 8)) * 8, x);
-                }
+                if (v < S::A_VECS)
+                    vec8_store<ST>(a + (v / (KC / 8)) * LDK + (v % (KC / 8)) * 8, sa.ok[j] ? sa.v[j] : vec8_zero<ST>());
             }
         } else if constexpr (AR) {
 #pragma unroll
@@ -387,10 +358,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(const typename P::Args args) 
                 const int blk = (tid + 256 * j) % S::A_BLKS;
                 const int mb = blk / (KC / 8), kb = blk % (KC / 8);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
+                for (int i = 0; i < 8; ++i)
                     if (!((sa.ok[j] >> i) & 1u)) sa.v[j][i] = vec8_zero<ST>();
-                    else if (P::A_SCALED) sa.v[j][i] = vec8_scale<ST>(sa.v[j][i], sa.sc[j][i]);
-                }
                 Vec8<ST> t[8];
                 transpose8(sa.v[j], t);
                 if (tid + 256 * j < S::A_BLKS) {

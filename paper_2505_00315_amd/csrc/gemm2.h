@@ -68,9 +68,10 @@
 //     column wn WTN + 16 j + lane % 16 of the tile (g = lane / 16).  The
 //     stage buffers are free by then (EPI_LDS bytes from smem on).
 //   a_tile_hook(args, m0, n0, a_tile, tid, state) / a_hook_done(args, m0, n0,
-//     tid, state): called by every thread after the MFMAs of each k chunk with
-//     that chunk's A tile in LDS (k-contiguous layout above), and once after
-//     the last chunk; `state` is one double per thread, zero at the start.
+//     tid, state): called by every thread for each k chunk with that chunk's A
+//     tile in LDS (k-contiguous layout above), before the MFMAs of the chunk's
+//     last 32-k step, and once after the last chunk; `state` is one double per
+//     thread, zero before the first.
 #pragma once
 
 #include "gemm.h"
@@ -120,26 +121,6 @@ __device__ __forceinline__ u32x2 lds_tr16(const unsigned char* p) {
 }
 // Wait for every outstanding LDS read of this wave.
 __device__ __forceinline__ void lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-// Wait until at most N LDS operations of this wave are outstanding (LDS
-// operations complete in issue order).
-template <int N>
-__device__ __forceinline__ void lds_wait_n() {
-    static_assert(N >= 0 && N <= 15, "lgkmcnt range");
-    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
-}
-// lds_wait_n<n>() for an n that is a constant after unrolling.
-template <int I = 0>
-__device__ __forceinline__ void lds_wait_le(int n) {
-    if constexpr (I < 15) {
-        if (n == I) {
-            lds_wait_n<I>();
-            return;
-        }
-        lds_wait_le<I + 1>(n);
-    } else {
-        lds_wait_n<15>();
-    }
-}
 // Make x depend on the preceding lds_wait() (an empty volatile statement that
 // claims to modify x keeps its consumers after the wait).
 __device__ __forceinline__ void lds_ready(u32x4& x) { asm volatile("" : "+v"(x)); }

@@ -29,7 +29,7 @@ template <typename ST, int DH, bool SMALL = false>
 struct OutProjPolicy {
     static constexpr int MT = SMALL ? 32 : 64, NT = SMALL ? 64 : 128, KC = sizeof(ST) == 2 ? DH : 32, WM = 2, WN = 2;
     static constexpr size_t EPI_LDS = 0;
-    static constexpr bool A_KCONTIG = true, B_KCONTIG = false, A_SCALED = false;
+    static constexpr bool A_KCONTIG = true, B_KCONTIG = false;
     struct Args {
         const ST* A;   // [B, H, k, DH], rows scaled by r
         const ST* Wo;  // [H, DH, d]
@@ -56,7 +56,7 @@ struct OutProjPolicy {
     __device__ static size_t ridx(const Args& a, int h, int m) {
         return ((size_t)(m / a.k) * a.H + h) * a.k + (m % a.k);
     }
-    __device__ static ARef a_row(const Args& a, int h, int m, float&) {
+    __device__ static ARef a_row(const Args& a, int h, int m) {
         if (m < 0 || m >= a.M) return {nullptr};
         return {a.A + ridx(a, h, m) * DH};
     }
@@ -66,7 +66,6 @@ struct OutProjPolicy {
     __device__ static RowInfo row_info(const Args&, int, int k) { return {k}; }
     __device__ static const ST* a_kaddr(const Args& a, int, const RowInfo&, int) { return a_fallback(a); }
     __device__ static bool a_kok(const Args&, int, const RowInfo&, int) { return false; }
-    __device__ static float a_kscale(const Args&, int, const RowInfo&) { return 1.f; }
     __device__ static const ST* b_kaddr(const Args& a, int h, const RowInfo& r, int n8) {
         return a.Wo + ((size_t)h * DH + max(r.k, 0)) * a.d + min(n8, a.d - 8);
     }
@@ -88,7 +87,7 @@ template <typename ST, int DH, bool SMALL = false>
 struct OutCombinePolicy {
     static constexpr int MT = SMALL ? 32 : 64, NT = SMALL ? 64 : 128, KC = 32, WM = 2, WN = 2;
     static constexpr size_t EPI_LDS = kCombineLds;
-    static constexpr bool A_KCONTIG = true, B_KCONTIG = false, A_SCALED = false;
+    static constexpr bool A_KCONTIG = true, B_KCONTIG = false;
     struct Args {
         const ST* Ad;        // [B, Hd, T, DH]
         const ST* Wod;       // [Hd, DH, d] = [Hd*DH, d]
@@ -114,7 +113,7 @@ struct OutCombinePolicy {
         n0 = (rem % a.ntiles) * NT;
     }
     __device__ static int k_size(const Args& a, int) { return a.Hd * DH; }
-    __device__ static ARef a_row(const Args& a, int b, int t, float&) {
+    __device__ static ARef a_row(const Args& a, int b, int t) {
         if (t < 0 || t >= a.T) return {nullptr};
         return {a.Ad + ((size_t)b * a.Hd * a.T + t) * DH};
     }
@@ -127,7 +126,6 @@ struct OutCombinePolicy {
     __device__ static RowInfo row_info(const Args&, int, int k) { return {k}; }
     __device__ static const ST* a_kaddr(const Args& a, int, const RowInfo&, int) { return a_fallback(a); }
     __device__ static bool a_kok(const Args&, int, const RowInfo&, int) { return false; }
-    __device__ static float a_kscale(const Args&, int, const RowInfo&) { return 1.f; }
     __device__ static const ST* b_kaddr(const Args& a, int, const RowInfo& r, int n8) {
         return a.Wod + (size_t)max(r.k, 0) * a.d + min(n8, a.d - 8);
     }
@@ -136,6 +134,7 @@ struct OutCombinePolicy {
     // 4 threads per token row, 32 columns each; MoSA rows added in head order.
     __device__ static void epilogue(const Args& a, int b, int m0, int n0, const float* Cs, int ldc, int tid,
                                     unsigned char* extra) {
+        static_assert(MT == 64 && NT == 128, "combine_tile covers a 64 x 128 tile");
         combine_tile<ST>(Cs, ldc, tid, b, m0, n0, a.T, a.d, a.H, a.k, a.slot, a.Xo, a.Y, a.accumulate,
                          reinterpret_cast<int16_t*>(extra));
     }

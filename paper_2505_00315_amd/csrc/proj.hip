@@ -27,7 +27,7 @@ struct QkvPolicy {
     static constexpr int MT = SMALL ? 32 : 64, NT = SMALL ? DH : 3 * DH, KC = 32, WM = 2, WN = 2;
     static constexpr int NTILES = 3 * DH / NT;
     static constexpr size_t EPI_LDS = 0;
-    static constexpr bool A_KCONTIG = true, B_KCONTIG = false, A_SCALED = false;
+    static constexpr bool A_KCONTIG = true, B_KCONTIG = false;
     struct Args {
         const ST* X;
         const int32_t* I;  // nullptr: identity (dense heads)
@@ -55,7 +55,7 @@ struct QkvPolicy {
         n0 = (rem % NTILES) * NT;
     }
     __device__ static int k_size(const Args& a, int) { return a.d; }
-    __device__ static ARef a_row(const Args& a, int h, int m, float&) {
+    __device__ static ARef a_row(const Args& a, int h, int m) {
         if (m < 0 || m >= a.M) return {nullptr};
         const int b = m / a.n, i = m % a.n;
         const int t = a.I ? a.I[((size_t)b * a.H + h) * a.n + i] : i;
@@ -67,7 +67,6 @@ struct QkvPolicy {
     __device__ static RowInfo row_info(const Args&, int, int k) { return {k}; }
     __device__ static const ST* a_kaddr(const Args& a, int, const RowInfo&, int) { return a_fallback(a); }
     __device__ static bool a_kok(const Args&, int, const RowInfo&, int) { return false; }
-    __device__ static float a_kscale(const Args&, int, const RowInfo&) { return 1.f; }
     // B[k][n] = W^{n / DH}_h[k][n % DH]: row k of the [d, DH] weight, n contiguous
     __device__ static const ST* b_kaddr(const Args& a, int h, const RowInfo& r, int n8) {
         const ST* W = n8 < DH ? a.W0 : (n8 < 2 * DH ? a.W1 : a.W2);

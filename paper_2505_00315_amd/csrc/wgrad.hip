@@ -36,7 +36,7 @@ struct WgradQkvPolicy {
     static constexpr int MT = 64, NT = SMALL ? DH : NALL, KC = sizeof(ST) == 2 ? 64 : 32, WM = SMALL ? 2 : 4, WN = 4 / WM;
     static constexpr int NTILES = (NALL + NT - 1) / NT;
     static constexpr size_t EPI_LDS = 0;
-    static constexpr bool A_KCONTIG = false, B_KCONTIG = false, A_SCALED = false, SPLITK = true;
+    static constexpr bool A_KCONTIG = false, B_KCONTIG = false, SPLITK = true;
     struct Args {
         const ST* X;
         const int32_t* I;
@@ -76,7 +76,7 @@ struct WgradQkvPolicy {
         kend = min(K, kbeg + a.cps * KC);
     }
     __device__ static int k_size(const Args& a, int) { return a.R; }
-    __device__ static ARef a_row(const Args&, int, int, float&) { return {}; }
+    __device__ static ARef a_row(const Args&, int, int) { return {}; }
     __device__ static const ST* a_elem(const Args&, int, const ARef&, int) { return nullptr; }
     __device__ static BRef b_row(const Args&, int, int) { return {}; }
     __device__ static const ST* b_elem(const Args&, int, const BRef&, int) { return nullptr; }
@@ -91,7 +91,6 @@ struct WgradQkvPolicy {
         return a.X + ((size_t)max(r.b, 0) * a.T + r.t) * a.d + min(m8, a.d - 8);
     }
     __device__ static bool a_kok(const Args& a, int, const RowInfo& r, int m8) { return r.b >= 0 && m8 < a.d; }
-    __device__ static float a_kscale(const Args&, int, const RowInfo&) { return 1.f; }
     // B[r][n] = dQ | dK | dV | (dz, 0...) of row r
     __device__ static const ST* b_kaddr(const Args& a, int, const RowInfo& r, int n8) {
         return n8 < 3 * DH ? a.dQKV + (size_t)r.ri * (3 * DH) + n8
@@ -159,7 +158,7 @@ template <typename ST, int DH, bool GATHER, bool SMALL = false>
 struct WgradOPolicy {
     static constexpr int MT = DH, NT = SMALL ? 64 : 128, KC = sizeof(ST) == 2 ? 64 : 32, WM = 2, WN = 2;
     static constexpr size_t EPI_LDS = 0;
-    static constexpr bool A_KCONTIG = false, B_KCONTIG = false, A_SCALED = false, SPLITK = true;
+    static constexpr bool A_KCONTIG = false, B_KCONTIG = false, SPLITK = true;
     struct Args {
         const ST* dY;
         const int32_t* I;
@@ -191,7 +190,7 @@ struct WgradOPolicy {
         kend = min(K, kbeg + a.cps * KC);
     }
     __device__ static int k_size(const Args& a, int) { return a.R; }
-    __device__ static ARef a_row(const Args&, int, int, float&) { return {}; }
+    __device__ static ARef a_row(const Args&, int, int) { return {}; }
     __device__ static const ST* a_elem(const Args&, int, const ARef&, int) { return nullptr; }
     __device__ static BRef b_row(const Args&, int, int) { return {}; }
     __device__ static const ST* b_elem(const Args&, int, const BRef&, int) { return nullptr; }
@@ -206,7 +205,6 @@ struct WgradOPolicy {
         return a.A + (size_t)r.ri * DH + m8;
     }
     __device__ static bool a_kok(const Args&, int, const RowInfo& r, int) { return r.b >= 0; }
-    __device__ static float a_kscale(const Args&, int, const RowInfo&) { return 1.f; }
     // B[r][c] = dY[b, I_r, c]
     __device__ static const ST* b_kaddr(const Args& a, int, const RowInfo& r, int n8) {
         return a.dY + ((size_t)max(r.b, 0) * a.T + r.t) * a.d + min(n8, a.d - 8);
