@@ -216,22 +216,31 @@ int aux_join(AuxStream* ax, hipStream_t main) {
 // stream and waited for on another about 13, a kernel launch 2.7): a layer whose
 // kernels take less than the host then runs slower on two streams than on
 // one, a larger one gains up to the shorter of its two chains.  So the line is
-// drawn by the work of both chains.  Measured with 4 dense and 12 MoSA heads,
-// d 1024, k = T / 32, bf16, one stream against two (us per pass; the latter on
-// a faster and a slower host): forward, 333 tokens 63 against 67-89, 2048 69 /
-// 67-90, 4096 72 / 68-86, 8192 86 / 82-84; forward and backward 136 / 161-196,
-// 166 / 167-210, 184 / 167-207, 244 / 226.  The line, 6 GFLOP of forward, lies
-// between 2048 and 4096 of those tokens; the MoSA heads' products count twice
-// (they run at about half the dense heads' rate).  fp32 chains are several
-// times longer at the same size and gain from 128 tokens on (108 against 84-89).
+// drawn by an estimate of the kernels' time, in units of the time at which
+// both forms are level: the work of both chains, W = dense + 2 MoSA GFLOP of
+// forward (the MoSA heads' products run at about half the dense heads' rate),
+// plus the serial loops of the two attentions over the rows of a head, which few
+// heads leave alone on the chip.  Fitted to one stream against two on 600 random
+// bf16 layers of 0.2 to 40 GFLOP (half of them of 1 to 4 sequences of 500 to
+// 8192 tokens), on a slower and a faster host: the training steps took 0.5 and
+// 0.7% more than with the better of the two each time, at worst 16% (by work
+// alone, from 6 GFLOP on: 1.3 and 1.0%, 31%), the forwards alone 1.3 and 0.9%
+// (2.7 and 1.7%).  4 dense and 12 MoSA heads, d 1024, k = T / 32, one stream
+// against two (us per forward / training step): 1 x 2048 tokens 75 against 84 / 189 against
+// 187, 4 x 1024 67, 78 / 174, 182, 2 x 2048 79, 79 / 206, 188, 1 x 4096 110, 86 /
+// 278, 251; one MoSA head with 1848 of 3142 tokens beside 5 dense ones, d 384,
+// dh 32, 279 / 195 per step.  fp32 chains are several times longer at the same
+// size and gain from 128 tokens on (108 against 84-89).
 bool two_streams(const mosa_shape* s) {
     if (s->heads == 0 || s->dense_heads == 0 || !combine_split_ok(s->d_model, s->heads)) return false;
     if (s->dtype == MOSA_F32) return true;
     const double B = s->batch, T = s->seq_len, d = s->d_model, dh = s->d_head, k = s->k;
-    const double keys = s->window > 0 && s->window < s->seq_len ? s->window : s->causal ? T / 2 : T;
+    const bool local = s->window > 0 && s->window < s->seq_len;
+    const double keys = local ? s->window : s->causal ? T / 2 : T;
     const double dense = B * s->dense_heads * T * dh * (8 * d + 4 * keys);
     const double mosa = B * s->heads * (k * dh * (8 * d + 4 * k) + 2 * T * d);
-    return dense + 2 * mosa >= 6e9;
+    const double work = (dense + 2 * mosa) * 1e-9, rows = (local ? s->window : T) + k;
+    return work / 13 + rows / 4000 >= 1;
 }
 
 }  // namespace

@@ -23,7 +23,7 @@ SMALL = dict(batch=2, seq_len=256, heads=4, k=16, d_head=64, d_model=128, dense_
 CASES = {
     "bf16_small": wl.small(name="streams_hybrid", **SMALL),
     "f32": wl.small(name="streams_hybrid_f32", dtype="f32", **SMALL),
-    "bf16_large": wl.small(name="streams_hybrid_large", batch=3, seq_len=1024, d_model=1024, heads=8, d_head=64, k=32,
+    "bf16_large": wl.small(name="streams_hybrid_large", batch=4, seq_len=1024, d_model=1024, heads=8, d_head=64, k=32,
                            dense_heads=4),
 }
 

@@ -1,9 +1,9 @@
-"""Layers with enough work for the library's auxiliary stream (bf16: 6 GFLOP of
-forward, the dense heads' plus twice the MoSA heads'; fp32: any), and layers just
-below that size, which stay on the caller's stream: the results equal those of
-the stage-timed calls (one stream, one serial order) bit for bit, for
-back-to-back calls, for calls that two host threads enqueue at the same time,
-and for calls on different inputs that share one saved and one scratch buffer."""
+"""Layers with enough work, or rows per head, for the library's auxiliary stream
+(fp32: any), and a layer just below that line, which stays on the caller's
+stream: the results equal those of the stage-timed calls (one stream, one
+serial order) bit for bit, for back-to-back calls, for calls that two host
+threads enqueue at the same time, and for calls on different inputs that share
+one saved and one scratch buffer."""
 import dataclasses
 import threading
 
@@ -17,8 +17,9 @@ from paper_2505_00315_amd import mosa
 pytestmark = pytest.mark.gpu
 
 CASES = {
-    "bf16_two": wl.small(batch=3, seq_len=1024, d_model=1024, heads=8, d_head=64, k=32, dense_heads=4),
-    "bf16_one": wl.small(batch=2, seq_len=1024, d_model=1024, heads=8, d_head=64, k=32, dense_heads=4),
+    "bf16_two": wl.small(batch=4, seq_len=1024, d_model=1024, heads=8, d_head=64, k=32, dense_heads=4),
+    "bf16_two_long_rows": wl.small(batch=1, seq_len=4500, d_model=64, heads=2, d_head=32, k=4000, dense_heads=1),
+    "bf16_one": wl.small(batch=3, seq_len=1024, d_model=1024, heads=8, d_head=64, k=32, dense_heads=4),
     "f32_two": wl.small(batch=2, seq_len=96, d_model=128, heads=3, d_head=32, k=20, dense_heads=2, dtype="f32"),
 }
 
