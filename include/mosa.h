@@ -20,10 +20,11 @@
  *     on the current device before each launch; mosa_forward_noalloc keeps
  *     the address of its static scratch; and the untimed forward and backward
  *     of a layer with both MoSA and dense heads run the dense heads' kernels,
- *     where there is enough work in them, on an auxiliary stream of the device (non-blocking, default priority,
- *     created at the first such call and kept until the process ends), forked
- *     from and joined back into `stream` with events inside the call, so the
- *     two sets of heads share the CUs.  The enqueue of such calls is
+ *     where the layer is large enough for that to be faster, on an auxiliary
+ *     stream of the device (non-blocking, default priority, created at the
+ *     first such call and kept until the process ends), forked from and joined
+ *     back into `stream` with events inside the call, so the two sets of heads
+ *     share the CUs.  The enqueue of such calls is
  *     serialised by a library mutex.  Calls from several host threads, on one
  *     device or several, do not interfere as long as they use different
  *     buffers.

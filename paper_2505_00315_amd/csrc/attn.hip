@@ -854,9 +854,13 @@ bool fa_geom(int dtype, int BH, int n, int dh, int causal, int window, FaGeom& G
     // one per CU, also up to 2048 rows: shorter than splits and their merge
     // (8 heads of 2048: 47.5 -> 44.8 us, 4 of 4096: 59.7 -> 62.7); and up to
     // 512 rows at any number, since so short a block is never split (3 heads
-    // of 500: 30.6 -> 27.0).  Two blocks of 128 per CU: forward of 8 dense heads
-    // of 1024, B = 8, 60.1 -> 51.3 us (QN = 2: 54.4); beside a large MoSA chain
-    // on the other stream (small S = 16 model, B = 16) 0.4% the other way.
+    // of 500: 30.6 -> 27.0).  At two blocks of 128 per CU QN = 1 gains alone
+    // (forward of 8 dense heads of 1024 rows, B = 8: 75.9 -> 71.7 us) and goes
+    // either way beside a MoSA chain on the other stream (4 dense heads, B = 16,
+    // T = 1024, forward / training step: 12 MoSA heads with k = 32 118.0 -> 114.2
+    // / 337 -> 334, 64 with 64 207.0 -> 200.5 / 556 -> 550, 109 with 64 310 -> 313
+    // / 776 -> 778, 256 with 16 233.5 -> 240.6 / 619 -> 627): the rule knows
+    // its own kernel only.
     const long long wg64 = (long long)BH * ((n + 63) / 64), wg128 = (long long)BH * ((n + 127) / 128);
     G.qn = window == 0 && wg128 <= 512 && (n <= 512 || wg64 >= (n <= 2048 ? 256 : 512)) ? 1 : 2;
     G.nqb = (n + fa_qb_rows(G) - 1) / fa_qb_rows(G);

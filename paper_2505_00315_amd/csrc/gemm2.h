@@ -92,9 +92,9 @@ __device__ __forceinline__ void lds_load16(const void* g, uint32_t base) {
 __device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(size_t)(const lds_u8*)p; }
 
 // Four 16-bit elements of a transposed 4 x 4 block (see above), issued as
-// inline assembly: the compiler cannot tell which LDS bytes the builtin form
-// reads and would wait for every direct-to-LDS load in flight before it.  The
-// result is not ready until lds_wait() below; nothing may read it earlier.
+// inline assembly for kernels that place the wait themselves, after work that
+// does not need the result.  It is not ready until lds_wait() below; nothing may
+// read it earlier.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u32x2 lds_read_tr16(const unsigned char* p) {

@@ -208,8 +208,8 @@ struct QkvPolicy2 {
 // same workgroup copies Q, K and V in bf16 into LDS and then runs the attention
 // of its groups (attn_lds.h, bit-identical to the separate attention kernel).
 // The bf16 tiles (50 KB at 128 rows of 64) fit in the stage buffers, so the
-// 80 KB of a workgroup leave room for two per CU, and the epilogue of one
-// overlaps the loop of the other.
+// 80 KB of a workgroup leave room for two per CU, and, with more tiles than
+// CUs, the epilogue of one overlaps the loop of the other.
 template <int DH, int RT = 128>
 struct QkvAttnPolicy : QkvPolicy2<DH, RT> {
     using ST = uint16_t;

@@ -618,7 +618,8 @@ int run_both(const uint16_t* X, const uint16_t* dY, const int32_t* I, const uint
     using PQ = WgradQkvPolicy2<DH, 64>;
     using PO = WgradOPolicy2<DH, 64>;
     const int R = B * n;
-    const int rq = wgrad2_table_rows<PQ>(R, d, (long long)B * T, (long long)R * H, DH), ro = wgrad2_table_rows<PO>(R, d, (long long)B * T, (long long)R * H, DH);
+    const long long tokens = (long long)B * T, sel = (long long)R * H;
+    const int rq = wgrad2_table_rows<PQ>(R, d, tokens, sel, DH), ro = wgrad2_table_rows<PO>(R, d, tokens, sel, DH);
     if (!rq || !ro) return 1;
     const int tl = d / 64, per = wgrad_tiles_per_wg(H, tl, R), wgs = (tl + per - 1) / per;
     typename PQ::Args aq{X, I, dQKV, dz16, dWq, dWk, dWv, dWr, nullptr, T, d, H, n, R, tl, wgs, per, make_fastdiv(n), dz};
@@ -637,7 +638,8 @@ int run_bwd_proj_t(const uint16_t* X, const uint16_t* dY, const int32_t* I, cons
                    uint16_t* dWr, uint16_t* dWo, uint16_t* dXs, hipStream_t stream) {
     using PX = DxProjRowPolicy<DH>;
     const int R = B * n;
-    const int rq = wgrad2_table_rows<PQ>(R, d, (long long)B * T, (long long)R * H, DH), ro = wgrad2_table_rows<PO>(R, d, (long long)B * T, (long long)R * H, DH);
+    const long long tokens = (long long)B * T, sel = (long long)R * H;
+    const int rq = wgrad2_table_rows<PQ>(R, d, tokens, sel, DH), ro = wgrad2_table_rows<PO>(R, d, tokens, sel, DH);
     typename PX::Args ax;
     int nx;
     if (!rq || !ro || !dx_row_args<DH>(dQKV, dz, Wq, Wk, Wv, Wr, B, d, H, n, dXs, ax, nx)) return 1;

@@ -81,8 +81,6 @@ def stage_work(w, with_backward=True):
         return out
     if H:
         add("bwd_out", X + H * dh * d * es + 2 * rows * dh * es + rows * 16, 2.0 * rows * d * dh)
-        add("attn_bwd_kv", 6 * rows * dh * es + rows * 8, 8.0 * dh * _pairs(k, w.causal) * B * H)
-        add("attn_bwd_q", 5 * rows * dh * es + rows * 8, 6.0 * dh * _pairs(k, w.causal) * B * H)
         # both passes: Q, K, V, dA read, dQ | dK | dV written, lse and D read;
         # five products over the allowed pairs (S recomputed, dP, dV, dK, dQ),
         # 2.5 times the forward's two
@@ -100,8 +98,6 @@ def stage_work(w, with_backward=True):
             out["wgrad"].flops + out["dx_proj"].flops)
     if Hd:
         add("bwd_out_dense", X + Hd * dh * d * es + 2 * R * dh * es + R * 4, 2.0 * R * d * dh)
-        add("attn_bwd_kv_dense", 6 * R * dh * es + R * 8, 8.0 * dh * _pairs(T, w.causal, w.window) * B * Hd)
-        add("attn_bwd_q_dense", 5 * R * dh * es + R * 8, 6.0 * dh * _pairs(T, w.causal, w.window) * B * Hd)
         add("attn_bwd_dense", 7 * R * dh * es + R * 8, 10.0 * dh * _pairs(T, w.causal, w.window) * B * Hd)
         add("wgrad_qkv_dense", X + 3 * R * dh * es + 3 * Hd * d * dh * es, 2.0 * R * d * 3 * dh)
         add("wgrad_o_dense", X + R * dh * es + Hd * dh * d * es, 2.0 * R * dh * d)
